@@ -458,6 +458,85 @@ __global__ void __launch_bounds__(kUpdThreads) dcgs2_update_kernel(cplx<double>*
   }
 }
 
+// The same pass for grids whose number of 2048-row chunks fills the chip badly: a workgroup
+// takes 64 Rows rows, its 8 waves 8 contiguous slices of the basis range, whose partial
+// combinations meet in LDS and are added in slice order.  Each lane keeps Vecs Rows loads in
+// flight.  Bound by memory (16 nd (j + 4) bytes) once the basis exceeds the caches.  Measured
+// in isolation, GB/s of those bytes, chunk kernel against this one:
+//   nd =   6,400, j = 800:   175 -> 3050 (Rows 1, Vecs 8)     4 chunks: 4 busy compute units
+//   nd =  25,281, j = 800:   615 -> 5590                      13 chunks
+//   nd = 102,400, j = 800:  2560 -> 6220                      50 chunks
+//   nd = 262,144, j = 800:  5350 -> 6170                      128 chunks
+//   nd = 404,496, j = 400:  6800 against 6020                 198 chunks: one full round, kept
+//   nd = 640,000, j = 400:  5470 -> 5920 (Rows 4, Vecs 4)     313 chunks: a nearly empty second round
+//   nd = 1,620,529, j = 250: 5340 -> 5770                     792 chunks
+constexpr int kSlices = kUpdThreads / kWave;
+
+template <int Rows, int Vecs>
+__global__ void __launch_bounds__(kUpdThreads) dcgs2_update_sliced_kernel(cplx<double>* __restrict__ basis,
+                                                                  long long bstride, long long ndof, StepRef sr,
+                                                                  const cplx<double>* __restrict__ ca,
+                                                                  const cplx<double>* __restrict__ cb, int cstride,
+                                                                  const cplx<double>* __restrict__ scal,
+                                                                  const int* __restrict__ done) {
+  constexpr int kRows = kWave * Rows;
+  const int rhs = blockIdx.y;
+  if (done && done[rhs]) return;
+  const int j = sr.get();
+  const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  __shared__ cplx<double> pa[kSlices][kRows], pb[kSlices][kRows];
+  cplx<double>* V = basis + rhs * bstride;
+  const long long row0 = (long long)blockIdx.x * kRows;
+  long long nc[Rows];   // rows past the end load the last one
+#pragma unroll
+  for (int r = 0; r < Rows; ++r) nc[r] = min(row0 + r * kWave + lane, ndof - 1);
+  const int lo = (int)((long long)j * wave / kSlices), hi = (int)((long long)j * (wave + 1) / kSlices);
+  const cplx<double>* __restrict__ xa = ca + (long long)rhs * cstride;
+  const cplx<double>* __restrict__ xb = cb + (long long)rhs * cstride;
+  cplx<double> acc_a[Rows], acc_b[Rows];
+#pragma unroll
+  for (int r = 0; r < Rows; ++r) { acc_a[r] = czero<double>(); acc_b[r] = czero<double>(); }
+  for (int q0 = lo; q0 < hi; q0 += Vecs) {
+    cplx<double> vv[Vecs][Rows];
+#pragma unroll
+    for (int q = 0; q < Vecs; ++q)
+#pragma unroll
+      for (int r = 0; r < Rows; ++r) vv[q][r] = load_stream(V + (long long)min(q0 + q, hi - 1) * ndof + nc[r]);
+#pragma unroll
+    for (int q = 0; q < Vecs; ++q) {
+      if (q0 + q < hi) {
+        const cplx<double> va = xa[q0 + q], vb = xb[q0 + q];
+#pragma unroll
+        for (int r = 0; r < Rows; ++r) {
+          acc_a[r] = cfma(vv[q][r], va, acc_a[r]);
+          acc_b[r] = cfma(vv[q][r], vb, acc_b[r]);
+        }
+      }
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < Rows; ++r) {
+    pa[wave][r * kWave + lane] = acc_a[r];
+    pb[wave][r * kWave + lane] = acc_b[r];
+  }
+  __syncthreads();
+  const int t = threadIdx.x;
+  const long long n = row0 + t;
+  if (t >= kRows || n >= ndof) return;
+  cplx<double> sa = pa[0][t], sb = pb[0][t];
+#pragma unroll
+  for (int s = 1; s < kSlices; ++s) {
+    sa = sa + pa[s][t];
+    sb = sb + pb[s][t];
+  }
+  const cplx<double> inv_alpha = scal[rhs * 4 + 0], e = scal[rhs * 4 + 1], inv_gamma = scal[rhs * 4 + 2];
+  cplx<double>* uj = V + (long long)j * ndof;
+  cplx<double>* w = V + (long long)(j + 1) * ndof;
+  const cplx<double> uo = uj[n];
+  uj[n] = inv_alpha.re * uo - sa;
+  w[n] = inv_gamma.re * (w[n] - sb - uo * e);
+}
+
 // Rotations 0..jc-1 applied to the column lcol[0..jc] by all threads of a 256-thread
 // workgroup.  Rotation i maps (x_i, col_{i+1}) to the rotated entry
 // c_i x_i + s_i col_{i+1} and the carried entry x_{i+1} = c_i col_{i+1} - conj(s_i) x_i,
@@ -816,15 +895,28 @@ hipError_t launch_dcgs2_step(const OuterState& s, StepRef sr, int jmax, long lon
   return hipGetLastError();
 }
 
+// The chunk kernel runs one workgroup per compute unit and is the faster one when its
+// workgroups nearly fill the 256 compute units in one round; below that units stand idle, above
+// it the last round does (figures at the sliced kernel).
+constexpr long long kChunkFillMin = 160, kChunkFillMax = 256;
+
 hipError_t launch_dcgs2_update(cplx<double>* basis, long long bstride, long long ndof, StepRef sr,
                                const cplx<double>* ca, const cplx<double>* cb, int cstride, const cplx<double>* scal,
                                int nrhs, const int* done, hipStream_t st) {
-  const int grid = (int)((ndof + kUpdChunkRows - 1) / kUpdChunkRows);
-  hipLaunchKernelGGL(dcgs2_update_kernel, dim3(grid, nrhs), dim3(kUpdThreads), 0, st, basis, bstride, ndof, sr,
-                     ca, cb, cstride, scal, done);
+  const long long chunks = (ndof + kUpdChunkRows - 1) / kUpdChunkRows, total = chunks * nrhs;
+  if (total >= kChunkFillMin && total <= kChunkFillMax) {
+    hipLaunchKernelGGL(dcgs2_update_kernel, dim3((unsigned)chunks, nrhs), dim3(kUpdThreads), 0, st, basis, bstride,
+                       ndof, sr, ca, cb, cstride, scal, done);
+  } else if (total < kChunkFillMin) {
+    hipLaunchKernelGGL((dcgs2_update_sliced_kernel<1, 8>), dim3((unsigned)((ndof + kWave - 1) / kWave), nrhs),
+                       dim3(kUpdThreads), 0, st, basis, bstride, ndof, sr, ca, cb, cstride, scal, done);
+  } else {
+    hipLaunchKernelGGL((dcgs2_update_sliced_kernel<4, 4>),
+                       dim3((unsigned)((ndof + 4 * kWave - 1) / (4 * kWave)), nrhs), dim3(kUpdThreads), 0, st, basis,
+                       bstride, ndof, sr, ca, cb, cstride, scal, done);
+  }
   return hipGetLastError();
 }
-
 
 hipError_t launch_backsolve(const OuterState& s, int nrhs, hipStream_t st) {
   hipLaunchKernelGGL(backsolve_kernel, dim3(nrhs), dim3(256), 0, st, s);
