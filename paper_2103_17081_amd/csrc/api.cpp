@@ -82,7 +82,7 @@ struct dd_handle {
   std::vector<int> cuts_x, cuts_y;
   std::vector<SubDesc> subs_h;
   long long nfine = 0, ncoarse = 0, nfac = 0;
-  int max_nj = 0, max_nc = 0;
+  int max_nj = 0, max_nc = 0, max_mx = 0;
   ddh::Consts cs{};
   std::vector<double> pivmin_h;
   // device
@@ -289,6 +289,7 @@ dd_status validate_and_plan(const dd_params* p, dd_handle* h) {
       d.oi0 = std::max(h->cuts_x[qx], 1); d.oi1 = h->cuts_x[qx + 1] - 1;
       d.oj0 = std::max(h->cuts_y[qy], 1); d.oj1 = h->cuts_y[qy + 1] - 1;
       d.mx = d.nx / 2; d.my = d.ny / 2;
+      d.inv_nx = ddh::row_reciprocal(d.nx); d.inv_mx = ddh::row_reciprocal(d.mx);
       d.defl = p->deflation;
       if (d.defl == DD_DEFLATION_LINEAR) {
         d.bmx = d.mx; d.bmy = d.my;
@@ -312,6 +313,7 @@ dd_status validate_and_plan(const dd_params* p, dd_handle* h) {
                                             : ddh::coarse_factor_size_paired(d.bmx, d.bmy);
       h->max_nj = std::max(h->max_nj, d.nx * d.ny);
       h->max_nc = std::max(h->max_nc, d.ncp);
+      h->max_mx = std::max(h->max_mx, d.mx);
       h->subs_h.push_back(d);
     }
   }
@@ -380,6 +382,7 @@ ddh::InnerArgs<T> inner_args(dd_handle* h) {
   a.max_nc = h->max_nc;
   a.tol = h->p.inner_tol;
   a.nt = h->inner_nt;
+  a.kind = ddh::coarse_kind(h->p.deflation, h->max_mx);
   a.order = h->lpt ? h->order : nullptr;
   return a;
 }
@@ -512,7 +515,8 @@ dd_status dd_setup(const dd_params* p, void* stream, dd_handle** out) {
     DD_TRY(h->alloc(&h->order, ord.size()));
     DD_HIP(hipMemcpy(h->order, ord.data(), ord.size() * sizeof(int), hipMemcpyHostToDevice));
     DD_TRY(h->alloc(&h->Ec, (size_t)h->ncoarse * ddh::coarse_coefs(h->p.deflation)));
-    DD_TRY(h->alloc(&h->fac, (size_t)h->nfac));
+    DD_TRY(h->alloc(&h->fac, (size_t)h->nfac + ddh::detail::kFactorPad));
+    DD_HIP(hipMemsetAsync(h->fac + h->nfac, 0, ddh::detail::kFactorPad * sizeof(cplx<double>), st));
     DD_TRY(h->alloc(&h->pivmin, 2 * (size_t)h->nsub));
     DD_HIP(ddh::launch_assemble_coarse(h->subs, h->nsub, h->cs, h->p.local_bc, h->Ec, st));
     if (h->p.deflation == DD_DEFLATION_LINEAR)

@@ -10,24 +10,24 @@
 //
 // Twisted block factorisation (elimination from both ends towards the middle row
 // p = (my - 1) / 2), without block pivoting:
-//   top,    i < p:  G_i = (D_i - L_i H_{i-1})^{-1},   H_i = G_i U_i;
-//   bottom, i > p:  K_i = (D_i - U_i J_{i+1})^{-1},   J_i = K_i L_i;
-//   middle:         M   = (D_p - L_p H_{p-1} - U_p J_{p+1})^{-1}.
+//   top,    i < p:  G_i = (D_i - L_i G_{i-1} U_{i-1})^{-1};
+//   bottom, i > p:  G_i = (D_i - U_i G_{i+1} L_{i+1})^{-1};
+//   middle:         G_p = (D_p - L_p G_{p-1} U_{p-1} - U_p G_{p+1} L_{p+1})^{-1}.
 // Solve E y = t:
-//   a_i = G_i (t_i - L_i a_{i-1}) for i < p  and  b_i = K_i (t_i - U_i b_{i+1}) for i > p,
-//   both sweeps side by side;  y_p = M (t_p - L_p a_{p-1} - U_p b_{p+1});
-//   y_i = a_i - H_i y_{i+1} (i < p)  and  y_i = b_i - J_i y_{i-1} (i > p), side by side.
-// That is my sequential dense mx x mx products (against 2 my - 1 for the one-ended block
-// LU), with the same 2 my - 1 stored blocks and the same bytes streamed.  Each inverse
-// is formed by Gauss-Jordan elimination with partial pivoting.
+//   a_i = G_i (t_i - L_i a_{i-1}) for i < p  and  a_i = G_i (t_i - U_i a_{i+1}) for i > p,
+//   both sweeps side by side;  y_p = G_p (t_p - L_p a_{p-1} - U_p a_{p+1});
+//   y_i = a_i - G_i U_i y_{i+1} (i < p)  and  y_i = a_i - G_i L_i y_{i-1} (i > p), side by side.
+// The couplings are tridiagonal, so applying them costs three products per unknown; keeping
+// G_i U_i and G_i L_i as dense blocks of their own would double the stored bytes.  Each
+// inverse is formed by Gauss-Jordan elimination with partial pivoting.
 //
-// Storage per subdomain at SubDesc::goff (complex<double>), mx*mx row-major blocks
-// (element (r, c) at r*mx + c): G_0..G_{p-1}, H_0..H_{p-1}, K_{p+1}..K_{my-1},
-// J_{p+1}..J_{my-1}, M.  E itself is kept as nine coefficients per coarse node, offset
+// Storage per subdomain at SubDesc::goff (complex<double>): G_0 .. G_{my-1}, each mx*mx with
+// element (r, c) at c*mx + r, so that consecutive lanes, which own consecutive rows, read
+// consecutive entries.  E itself is kept as nine coefficients per coarse node, offset
 // index o = 3*(dy+1) + (dx+1) for the neighbour (cx+dx, cy+dy).
 //
 // The exact local solves factor the local matrices B_j the same way (block size nx, ny
-// block rows), through the same set-up kernel and solve.
+// block rows), through the same set-up kernel.
 #pragma once
 
 #include "common.hpp"
@@ -37,16 +37,11 @@ namespace ddh {
 constexpr int kMaxMx = 128;   // largest coarse block (mx) the kernels support
 
 __host__ __device__ __forceinline__ long long coarse_factor_size(int mx, int my) {
-  return (long long)(2 * my - 1) * mx * mx;
+  return (long long)my * mx * mx;
 }
 
-// Twisted factorisation: middle row and block offsets (in units of mx*mx blocks).
+// Middle row of the twisted factorisation.
 __host__ __device__ __forceinline__ int twist_row(int my) { return (my - 1) / 2; }
-__host__ __device__ __forceinline__ int tw_G(int i) { return i; }
-__host__ __device__ __forceinline__ int tw_H(int p, int i) { return p + i; }
-__host__ __device__ __forceinline__ int tw_K(int p, int i) { return p + i - 1; }
-__host__ __device__ __forceinline__ int tw_J(int my, int i) { return my + i - 2; }
-__host__ __device__ __forceinline__ int tw_M(int my) { return 2 * my - 2; }
 
 // Bezier deflation couples coarse nodes up to two rows apart, so its E is taken as
 // block tridiagonal over pairs of coarse rows (block size bmx = 2 mx, bmy block rows; an
@@ -74,79 +69,296 @@ __host__ __device__ __forceinline__ int coarse_group_lanes(int mx) {
 }
 
 // Copy the three lower couplings of every coarse node of E (neighbours (cx-1..cx+1,
-// cy-1), offsets o = 0, 1, 2) into LDS: lc[3 c + e].  Workgroup-cooperative; the
-// caller synchronises before the first coarse_solve.
+// cy-1), offsets o = 0, 1, 2; 0 outside the coarse grid) into LDS: lc[3 c + e], and a zero after
+// the last one (lower_entries in all).  Workgroup-cooperative; the caller synchronises before the
+// first coarse_solve.
+__host__ __device__ __forceinline__ constexpr size_t lower_entries(size_t nc) { return 3 * nc + 1; }
 __device__ __forceinline__ void stage_lower(const SubDesc& d, const cplx<double>* __restrict__ Ec,
                                             cplx<double>* lc) {
   if (d.defl != 0) return;   // the paired (Bezier) solve keeps its couplings with the factors
   const int nc = d.mx * d.my;
   const cplx<double>* ec = Ec + d.coff * 9;
   for (int e = threadIdx.x; e < 3 * nc; e += blockDim.x) lc[e] = ec[(size_t)(e / 3) * 9 + e % 3];
+  if (threadIdx.x == 0) lc[3 * nc] = czero<double>();
 }
 
 namespace detail {
 
 // ---- twisted solve of E (linear deflation; layout above) ----------------------------
-// The workgroup is split into two halves of Half threads: half 0 runs the top sweep
-// (and the middle row), half 1 the bottom sweep.  Step s of the solve:
-//   s < nf = my - 1 - p:  a_s (top, if s < p) and b_{my-1-s} (bottom);
-//   s = nf:               the coupled middle right-hand side, then y_p;
-//   s > nf:               y_{p-1-(s-nf-1)} (top) and y_{p+1+(s-nf-1)} (bottom).
-// a, b and y share the LDS array `a` (row i at a + i mx); t is used as scratch.
+// a and y share the LDS array `a` (row i at a + i mx); t is used as scratch.
 // lower(i, c, e): coupling of unknown c of row i to unknown c+e-1 of row i-1 (for E, the
 // staged lc[3 (i mx + c) + e]); the upper coupling of unknown c of row i-1 to c+e-1 of
 // row i is lower(i, c+e-1, 2-e).
-
-// Factor block (mx*mx units) half h reads at step s, or -1.
-__device__ __forceinline__ int tw_step_block(int h, int s, int p, int my) {
-  const int nf = my - 1 - p;
-  if (s < nf) return h == 0 ? (s < p ? tw_G(s) : -1) : tw_K(p, my - 1 - s);
-  if (s == nf) return h == 0 ? tw_M(my) : -1;
-  const int b = s - nf - 1;
-  if (h == 0) return p - 1 - b >= 0 ? tw_H(p, p - 1 - b) : -1;
-  return p + 1 + b <= my - 1 ? tw_J(my, p + 1 + b) : -1;
-}
 
 // `v` if `keep`, else 0 (a select, not a branch).
 __device__ __forceinline__ cplx<double> keep_c(bool keep, cplx<double> v) {
   return cplx<double>{keep ? v.re : 0.0, keep ? v.im : 0.0};
 }
 
-// t_{i+1} -= L_{i+1} a_i (top) for unknown c.  Neighbours outside the row are read at c
-// with a zero coupling, so all operands are loaded without branches (same sum).
+// The three couplings of unknown c of row i to row i + dir (dir -1 or +1), unknowns c-1, c,
+// c+1; those outside the row are 0 and read at c.
 template <typename Lower>
-__device__ __forceinline__ void tw_couple_down(int mx, Lower lower, int i, int c, cplx<double>* t,
-                                               const cplx<double>* a) {
-  const cplx<double>* ap = a + i * mx + c;
+__device__ __forceinline__ void tw_couplings(int mx, Lower lower, int i, int c, int dir, cplx<double> k[3]) {
   const bool lo = c > 0, hi = c < mx - 1;
-  const cplx<double> l0 = keep_c(lo, lower(i + 1, c, 0)), l2 = keep_c(hi, lower(i + 1, c, 2));
-  const cplx<double> am = ap[lo ? -1 : 0], a0 = ap[0], ap1 = ap[hi ? 1 : 0];
-  cplx<double> v = t[(i + 1) * mx + c] - lower(i + 1, c, 1) * a0;
-  v = v - l0 * am;
-  v = v - l2 * ap1;
-  t[(i + 1) * mx + c] = v;
+  if (dir < 0) {
+    k[0] = keep_c(lo, lower(i, c, 0));
+    k[1] = lower(i, c, 1);
+    k[2] = keep_c(hi, lower(i, c, 2));
+  } else {
+    k[0] = keep_c(lo, lower(i + 1, lo ? c - 1 : c, 2));
+    k[1] = lower(i + 1, c, 1);
+    k[2] = keep_c(hi, lower(i + 1, hi ? c + 1 : c, 0));
+  }
 }
 
-// t_{i-1} -= U_{i-1} b_i (bottom) for unknown c, U_{i-1} read as L_i^T.
+// v - (couplings of unknown c of row i to row i + dir) x, x that row's values.
 template <typename Lower>
-__device__ __forceinline__ void tw_couple_up(int mx, Lower lower, int i, int c, cplx<double>* t,
-                                             const cplx<double>* a) {
-  const cplx<double>* bp = a + i * mx + c;
-  const bool lo = c > 0, hi = c < mx - 1;
-  const cplx<double> u0 = keep_c(lo, lower(i, lo ? c - 1 : c, 2)), u2 = keep_c(hi, lower(i, hi ? c + 1 : c, 0));
-  const cplx<double> bm = bp[lo ? -1 : 0], b0 = bp[0], bp1 = bp[hi ? 1 : 0];
-  cplx<double> v = t[(i - 1) * mx + c] - lower(i, c, 1) * b0;
-  v = v - u0 * bm;
-  v = v - u2 * bp1;
-  t[(i - 1) * mx + c] = v;
+__device__ __forceinline__ cplx<double> tw_couple(int mx, Lower lower, int i, int c, int dir, cplx<double> v,
+                                                  const cplx<double>* x) {
+  cplx<double> k[3];
+  tw_couplings(mx, lower, i, c, dir, k);
+  const cplx<double> xm = x[c > 0 ? c - 1 : c], x0 = x[c], xp = x[c < mx - 1 ? c + 1 : c];
+  v = v - k[1] * x0;
+  v = v - k[0] * xm;
+  return v - k[2] * xp;
 }
 
-// t_p -= L_p a_{p-1} + U_p b_{p+1} for unknown c.
+// Orders this wave's LDS accesses before those after it (the LDS unit serves one wave's
+// operations in order, so nothing has to be waited for).
+__device__ __forceinline__ void wave_lds_order() { asm volatile("" ::: "memory"); }
+
+// Sum of v over the lanes l, l + 64 / L, l + 2 * 64 / L, ... (L = 2 or 4); all of them get it.
+template <int L>
+__device__ __forceinline__ double column_sum(double v) {
+  if constexpr (L == 4) v = fold16(v, v);
+  return fold32(v, v);
+}
+
+// Value of the neighbouring row's lane (row - 1 / row + 1); the rows of a wave are its lanes
+// modulo 64 / L: 16-lane rows of the wave for L = 4, the half wave for L = 2 (the lane past the
+// end gets another column group's value, always multiplied by a coupling of 0).
+constexpr int kDppRowShr1 = 0x111, kDppRowShl1 = 0x101, kDppWaveShr1 = 0x138, kDppWaveShl1 = 0x130;
+template <int L>
+__device__ __forceinline__ cplx<double> row_below(cplx<double> v) {
+  constexpr int ctrl = L == 4 ? kDppRowShr1 : kDppWaveShr1;
+  return cplx<double>{dpp_f64<ctrl>(v.re), dpp_f64<ctrl>(v.im)};
+}
+template <int L>
+__device__ __forceinline__ cplx<double> row_above(cplx<double> v) {
+  constexpr int ctrl = L == 4 ? kDppRowShl1 : kDppWaveShl1;
+  return cplx<double>{dpp_f64<ctrl>(v.re), dpp_f64<ctrl>(v.im)};
+}
+
+// Entries allocated (and zeroed) after the last factor block, for the columns a lane of the chain
+// reads past the end of a block.
+constexpr int kFactorPad = 32 * 32;
+
+// Entries of the LDS scratch of coarse_solve (one vector per half of the workgroup).
+constexpr int kChainScratch = 2 * 32;
+
+// The solve as a chain of waves, mx <= L Q and mx <= 64 / L.  The waves of a workgroup form two
+// halves, one per sweep; each wave owns `per` consecutive block rows of its half's sweep and
+// holds their G_i in registers from the forward to the backward pass (Slots blocks; further
+// ones are fetched again when a slot is free), all loads issued before the first step.  A step
+// is one wave's work: lane r + (64 / L) g owns row r and the columns g + q L, forms the coupled
+// right-hand side with its neighbours' values (DPP), shares it through LDS with its own wave
+// only, multiplies and sums over g with lane swaps.  Only handing the sweep to the next wave
+// takes a workgroup barrier, instead of one or two for every block row.
+//
+// What bounds it: the dependent steps (my of them forward and backward, 0.2 us each: an LDS
+// round trip, 4 Q FP64 FMAs, the lane swaps), no longer the latency of the factor loads.
+template <int NT, int L, int Q, int Slots>
+struct CoarseChain {
+  static constexpr int kHalfWaves = NT / (2 * kWave);
+  static constexpr int kBatch = 4;
+  cplx<double> G[Slots][Q];
+  int mx, my, p, half, pos, per, first, count, r, g;
+  unsigned off;
+
+  // block row of position s of this wave's half (top: 0 .. p, bottom: my - 1 .. p + 1)
+  __device__ __forceinline__ int row_of(int s) const { return half ? my - 1 - s : s; }
+
+  // Columns past the block read what follows it in the factor array (kFactorPad entries follow
+  // the last block) and multiply zeros.
+  __device__ __forceinline__ void load(cplx<double> (&dst)[Q], const cplx<double>* __restrict__ F, int s) {
+    const cplx<double>* B = F + (size_t)(row_of(s) * mx * mx);   // uniform: scalar base, one lane offset
+#pragma unroll
+    for (int q = 0; q < Q; ++q) dst[q] = (B + q * L * mx)[off];
+  }
+
+  // Split the block rows over the waves and issue the loads of the first blocks.
+  __device__ __forceinline__ void start(int mx_, int my_, const cplx<double>* __restrict__ F) {
+    mx = mx_;
+    my = my_;
+    p = twist_row(my);
+    const int tid = fresh_tid(), lane = tid % kWave, wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    half = wave / kHalfWaves;
+    // the halves' active waves sit on different SIMDs (waves w and w + 4 share one)
+    pos = half ? (wave + kHalfWaves / 2) % kHalfWaves : wave;
+    r = min(lane % (kWave / L), mx - 1);   // spare lanes repeat the last row
+    g = lane / (kWave / L);
+    off = (unsigned)(g * mx + r);
+    const int longest = max(p + 1, my - 1 - p);
+    per = max((longest + kHalfWaves - 1) / kHalfWaves, min(longest, Slots));
+    const int n = half ? my - 1 - p : p + 1;
+    first = pos * per;
+    count = max(0, min(per, n - first));
+#pragma unroll
+    for (int k = 0; k < Slots; ++k)
+      if (k < count) load(G[k], F, first + k);
+  }
+
+  // What a step reads besides the factor block: the couplings of unknown r of block row i to row
+  // i + dir and entry r of row i of `rhs`.  Read one step ahead: it does not depend on the chain.
+  struct Inputs {
+    cplx<double> k[3], rhs;
+  };
+  __device__ __forceinline__ Inputs fetch(const cplx<double>* lc, int i, int dir, const cplx<double>* rhs) const {
+    // lower couplings of row i, or those of row i + 1 transposed; the ones that leave the row are
+    // stored zeros (the last entry is stage_lower's padding)
+    const cplx<double>* e = lc + 3 * (min(i + (dir > 0 ? 1 : 0), my - 1) * mx + r);
+    Inputs in;
+    in.k[0] = e[dir > 0 ? -1 : 0];
+    in.k[1] = e[1];
+    in.k[2] = e[dir > 0 ? 3 : 2];
+    in.rhs = rhs[i * mx + r];
+    return in;
+  }
+
+  // Couplings of the step's row to the neighbouring block row's values.
+  __device__ __forceinline__ cplx<double> coupled(const Inputs& in, cplx<double> prev) const {
+    const cplx<double> xm = row_below<L>(prev), xp = row_above<L>(prev);
+    cplx<double> v = in.k[1] * prev;
+    v = cfma(in.k[0], xm, v);
+    return cfma(in.k[2], xp, v);
+  }
+
+  // Row r of B x, x entry r held as v; `next` is filled while the product runs.
+  template <typename Next>
+  __device__ __forceinline__ cplx<double> product(const cplx<double> (&B)[Q], cplx<double> v, cplx<double>* xb,
+                                                  Next next) const {
+    const int lane = threadIdx.x % kWave;
+    wave_lds_order();
+    if (g == 0) xb[lane] = keep_c(lane < mx, v);   // columns past the row multiply zeros
+    wave_lds_order();
+    // x in batches, one ahead of the products: few values live at a time
+    cplx<double> acc[2] = {czero<double>(), czero<double>()}, x[2][kBatch];
+    auto read = [&](int b) {
+#pragma unroll
+      for (int q = b * kBatch; q < (b + 1) * kBatch && q < Q; ++q) x[b % 2][q - b * kBatch] = xb[g + q * L];
+    };
+    read(0);
+#pragma unroll
+    for (int b = 0; b * kBatch < Q; ++b) {
+      if ((b + 1) * kBatch < Q) read(b + 1);
+      if ((b + 1) * kBatch >= Q) next();
+      wave_lds_order();
+#pragma unroll
+      for (int q = b * kBatch; q < (b + 1) * kBatch && q < Q; ++q)
+        acc[q % 2] = cfma(B[q], x[b % 2][q - b * kBatch], acc[q % 2]);
+    }
+    const cplx<double> acc0 = acc[0] + acc[1];
+    return cplx<double>{column_sum<L>(acc0.re), column_sum<L>(acc0.im)};
+  }
+
+  __device__ __forceinline__ void solve(const cplx<double>* __restrict__ F, const cplx<double>* lc, cplx<double>* t,
+                                        cplx<double>* a, cplx<double>* scratch) {
+    const bool writes = threadIdx.x % kWave < mx && g == 0;
+    cplx<double>* xb = scratch + half * 32;
+    const int fdir = half ? 1 : -1;
+    const int rounds = (max(p + 1, my - 1 - p) + per - 1) / per;
+    const int last = half ? first + count - 1 : min(first + count, p) - 1;   // last position but the middle row
+    cplx<double> prev = czero<double>();   // entry r of the neighbouring block row (0 before the first)
+    // forward: a_i = G_i (t_i - couplings to the row before it in the sweep)
+    for (int w = 0; w < rounds; ++w) {
+      if (w == pos && last >= first) {
+        Inputs in = fetch(lc, row_of(first), fdir, t);
+        if (first > 0) prev = a[row_of(first - 1) * mx + r];
+        for (int u0 = 0; u0 < count; u0 += Slots) {
+#pragma unroll
+          for (int k = 0; k < Slots; ++k) {
+            const int u = u0 + k, s = first + u;
+            if (s <= last) {
+              const cplx<double> v = in.rhs - coupled(in, prev);
+              prev = product(G[k], v, xb, [&]() { in = fetch(lc, row_of(min(s + 1, last)), fdir, t); });
+              if (writes) a[row_of(s) * mx + r] = prev;
+              if (u + Slots < count) load(G[k], F, s + Slots);
+            }
+          }
+        }
+      }
+      lds_barrier();
+    }
+    // the middle row, by the wave that owns it
+    if (!half && count > 0 && first + count - 1 == p) {
+      cplx<double> v = t[p * mx + r];
+      auto lower = [lc, this](int i, int c, int e) { return lc[3 * (i * mx + c) + e]; };
+      if (p > 0) v = tw_couple(mx, lower, p, r, -1, v, a + (p - 1) * mx);
+      if (p < my - 1) v = tw_couple(mx, lower, p, r, 1, v, a + (p + 1) * mx);
+      const int km = (count - 1) % Slots;
+      cplx<double> y = czero<double>();
+#pragma unroll
+      for (int k = 0; k < Slots; ++k)
+        if (k == km) {
+          y = product(G[k], v, xb, []() {});
+          if (count - 1 >= Slots) load(G[k], F, p - Slots);
+        }
+      if (writes) a[p * mx + r] = y;
+    }
+    lds_barrier();
+    // backward: y_i = a_i - G_i (couplings to the row after it in the sweep)
+    for (int w = rounds - 1; w >= 0; --w) {
+      if (w == pos && last >= first) {
+        Inputs in = fetch(lc, row_of(last), -fdir, a);
+        prev = a[row_of(last + 1) * mx + r];
+        for (int u0 = (count - 1) / Slots * Slots; u0 >= 0; u0 -= Slots) {
+#pragma unroll
+          for (int k = Slots - 1; k >= 0; --k) {
+            const int u = u0 + k, s = first + u;
+            if (s <= last) {
+              const cplx<double> ai = in.rhs, v = coupled(in, prev);
+              prev = ai - product(G[k], v, xb, [&]() { in = fetch(lc, row_of(max(s - 1, first)), -fdir, a); });
+              if (writes) a[row_of(s) * mx + r] = prev;
+              if (u >= Slots) load(G[k], F, s - Slots);
+            }
+          }
+        }
+      }
+      lds_barrier();
+    }
+  }
+};
+
+// The same steps for wider block rows, one step of both sweeps at a time for the whole
+// workgroup (half 0 the top sweep and the middle row, half 1 the bottom sweep):
+//   s < nf = my - 1 - p:  a_s (top, if s < p) and a_{my-1-s} (bottom);
+//   s = nf:               y_p;
+//   s > nf:               y_{p-1-(s-nf-1)} (top) and y_{p+1+(s-nf-1)} (bottom).
+// A step forms the coupled right-hand side in `t` once per unknown, then the block product.
+
+// Block row of half h at step s, or -1.
+__device__ __forceinline__ int tw_step_row(int h, int s, int p, int my) {
+  const int nf = my - 1 - p;
+  if (s < nf) return h == 0 ? (s < p ? s : -1) : my - 1 - s;
+  if (s == nf) return h == 0 ? p : -1;
+  const int i = h == 0 ? p - (s - nf) : p + (s - nf);
+  return i >= 0 && i < my ? i : -1;
+}
+
+// Coupled right-hand side of unknown c of row i at step s, into t.
 template <typename Lower>
-__device__ __forceinline__ void tw_couple_middle(int mx, int my, int p, Lower lower, int c, cplx<double>* t,
-                                                 const cplx<double>* a) {
-  if (p > 0) tw_couple_down(mx, lower, p - 1, c, t, a);
-  if (p < my - 1) tw_couple_up(mx, lower, p + 1, c, t, a);
+__device__ __forceinline__ void tw_step_rhs(int mx, int my, int p, Lower lower, int h, int s, int i, int c,
+                                            cplx<double>* t, const cplx<double>* a) {
+  const int nf = my - 1 - p;
+  if (s <= nf) {
+    cplx<double> v = t[i * mx + c];
+    if (i <= p && i > 0) v = tw_couple(mx, lower, i, c, -1, v, a + (i - 1) * mx);
+    if (i >= p && i < my - 1) v = tw_couple(mx, lower, i, c, 1, v, a + (i + 1) * mx);
+    t[i * mx + c] = v;
+  } else {
+    const int dir = h == 0 ? 1 : -1;
+    t[i * mx + c] = czero<double>() - tw_couple(mx, lower, i, c, dir, czero<double>(), a + (i + dir) * mx);
+  }
 }
 
 // Factor blocks of Depth consecutive steps are loaded together into registers (clamped
@@ -167,13 +379,13 @@ __device__ __forceinline__ void twisted_solve_ring(int mx, int my, const cplx<do
   for (int q = 0; q < Q; ++q) {
     ok[q] = active && l + q * L < mx;
     col[q] = ok[q] ? l + q * L : 0;
-    eoff[q] = ok[q] ? r * mx + col[q] : 0;
+    eoff[q] = ok[q] ? col[q] * mx + r : 0;
   }
   cplx<double> ring[Depth][Q];
   for (int s0 = 0; s0 < nsteps; s0 += Depth) {
 #pragma unroll
     for (int u = 0; u < Depth; ++u) {
-      const int blk = max(tw_step_block(h, s0 + u, p, my), 0);
+      const int blk = max(tw_step_row(h, s0 + u, p, my), 0);
 #pragma unroll
       for (int q = 0; q < Q; ++q) {
         const cplx<double> fv = F[(size_t)blk * mm + eoff[q]];
@@ -185,57 +397,18 @@ __device__ __forceinline__ void twisted_solve_ring(int mx, int my, const cplx<do
     for (int u = 0; u < Depth; ++u) {
       const int s = s0 + u;
       if (s >= nsteps) break;
-      if (s < nf) {
-        // a_s = G_s t_s (top, s < p), b_i = K_i t_i (bottom, i = my-1-s)
-        const int i = h == 0 ? s : my - 1 - s;
-        const bool on = h == 1 || s < p;
-        cplx<double> acc = czero<double>();
-        if (on) {
+      const int i = tw_step_row(h, s, p, my);
+      if (i >= 0 && ht < mx) tw_step_rhs(mx, my, p, lower, h, s, i, ht, t, a);
+      lds_barrier();
+      cplx<double> acc = czero<double>();
+      if (i >= 0) {
 #pragma unroll
-          for (int q = 0; q < Q; ++q) acc = cfma(ring[u][q], t[i * mx + col[q]], acc);
-        }
-        acc.re = row_sum<L>(acc.re);
-        acc.im = row_sum<L>(acc.im);
-        if (on && active && l == 0) a[i * mx + r] = acc;
-        lds_barrier();
-        if (ht < mx) {
-          if (h == 0) {
-            if (s + 1 < p) tw_couple_down(mx, lower, s, ht, t, a);
-          } else {
-            if (i - 1 > p) tw_couple_up(mx, lower, i, ht, t, a);
-          }
-        }
-        lds_barrier();
-      } else if (s == nf) {
-        if (h == 0 && ht < mx) tw_couple_middle(mx, my, p, lower, ht, t, a);
-        lds_barrier();
-        cplx<double> acc = czero<double>();
-        if (h == 0) {
-#pragma unroll
-          for (int q = 0; q < Q; ++q) acc = cfma(ring[u][q], t[p * mx + col[q]], acc);
-        }
-        acc.re = row_sum<L>(acc.re);
-        acc.im = row_sum<L>(acc.im);
-        if (h == 0 && active && l == 0) a[p * mx + r] = acc;
-        lds_barrier();
-      } else {
-        // y_i = a_i - H_i y_{i+1} (top), y_i = b_i - J_i y_{i-1} (bottom); a_i is read
-        // before the product so that its load overlaps it
-        const int b = s - nf - 1;
-        const int i = h == 0 ? p - 1 - b : p + 1 + b;
-        const bool on = h == 0 ? i >= 0 : i <= my - 1;
-        const int src = h == 0 ? i + 1 : i - 1;
-        const cplx<double> ai = a[(on ? i : p) * mx + (active ? r : 0)];
-        cplx<double> acc = czero<double>();
-        if (on) {
-#pragma unroll
-          for (int q = 0; q < Q; ++q) acc = cfma(ring[u][q], a[src * mx + col[q]], acc);
-        }
-        acc.re = row_sum<L>(acc.re);
-        acc.im = row_sum<L>(acc.im);
-        if (on && active && l == 0) a[i * mx + r] = ai - acc;
-        lds_barrier();
+        for (int q = 0; q < Q; ++q) acc = cfma(ring[u][q], t[i * mx + col[q]], acc);
       }
+      acc.re = row_sum<L>(acc.re);
+      acc.im = row_sum<L>(acc.im);
+      if (i >= 0 && active && l == 0) a[i * mx + r] = s <= nf ? acc : a[i * mx + r] - acc;
+      lds_barrier();
     }
   }
 }
@@ -257,41 +430,16 @@ __device__ __forceinline__ void twisted_solve_plain(int mx, int my, const cplx<d
     }
     return v;
   };
-  auto product = [&](int blk, const cplx<double>* x) {
-    cplx<double> acc = czero<double>();
-    if (active)
-      for (int c = l; c < mx; c += L) acc = cfma(F[(size_t)blk * mm + r * mx + c], x[c], acc);
-    return gsum(acc);
-  };
   for (int s = 0; s < nsteps; ++s) {
-    const int blk = tw_step_block(h, s, p, my);
-    if (s < nf) {
-      const int i = h == 0 ? s : my - 1 - s;
-      const cplx<double> acc = product(max(blk, 0), t + i * mx);
-      if (blk >= 0 && active && l == 0) a[i * mx + r] = acc;
-      lds_barrier();
-      if (ht < mx) {
-        if (h == 0) {
-          if (s + 1 < p) tw_couple_down(mx, lower, s, ht, t, a);
-        } else {
-          if (i - 1 > p) tw_couple_up(mx, lower, i, ht, t, a);
-        }
-      }
-      lds_barrier();
-    } else if (s == nf) {
-      if (h == 0 && ht < mx) tw_couple_middle(mx, my, p, lower, ht, t, a);
-      lds_barrier();
-      const cplx<double> acc = product(tw_M(my), t + p * mx);
-      if (h == 0 && active && l == 0) a[p * mx + r] = acc;
-      lds_barrier();
-    } else {
-      const int b = s - nf - 1;
-      const int i = h == 0 ? p - 1 - b : p + 1 + b;
-      const int src = h == 0 ? i + 1 : i - 1;
-      const cplx<double> acc = blk >= 0 ? product(blk, a + src * mx) : czero<double>();
-      if (blk >= 0 && active && l == 0) a[i * mx + r] = a[i * mx + r] - acc;
-      lds_barrier();
-    }
+    const int i = tw_step_row(h, s, p, my);
+    if (i >= 0 && ht < mx) tw_step_rhs(mx, my, p, lower, h, s, i, ht, t, a);
+    lds_barrier();
+    cplx<double> acc = czero<double>();
+    if (i >= 0 && active)
+      for (int c = l; c < mx; c += L) acc = cfma(F[(size_t)i * mm + c * mx + r], t[i * mx + c], acc);
+    acc = gsum(acc);
+    if (i >= 0 && active && l == 0) a[i * mx + r] = s <= nf ? acc : a[i * mx + r] - acc;
+    lds_barrier();
   }
 }
 
@@ -342,32 +490,52 @@ __device__ __forceinline__ void coarse_solve_paired(const SubDesc& d, const cplx
 
 }  // namespace detail
 
+// Form of the coarse solve, compiled into kernels of their own (a kernel's registers are those of
+// its largest form): the wave chain with 4 lanes per row (linear deflation, mx <= 16), with 2 lanes of
+// 13 columns (mx <= 26), or the step-by-step forms and the paired rows of Bezier deflation.
+enum CoarseKind { kCoarseNarrow = 0, kCoarseChain = 1, kCoarseGeneral = 2 };
+constexpr int kNarrowMx = 16, kChainMx = 26;
+
+// The form that covers every subdomain of a set with these block widths.
+__host__ __device__ __forceinline__ int coarse_kind(int defl, int max_mx) {
+  return defl != 0 || max_mx > kChainMx ? kCoarseGeneral : (max_mx <= kNarrowMx ? kCoarseNarrow : kCoarseChain);
+}
+
 // y = E^{-1} t for one subdomain, workgroup-cooperative (NT threads).  `t` and `a`
 // are d.ncp-entry LDS arrays (must not alias; entries from mx * my on are zero
 // padding); the result overwrites `a` and `t` is used as scratch (its content is
-// lost); `lc` holds the lower couplings staged by stage_lower (linear deflation).
-// `fac` is the handle's factor base (the subdomain offset is applied here).  Block row
-// r of each step is handled by a group of lanes that split its columns and reduce with
-// DPP row operations, so every step costs one LDS-only barrier (two for the forward
-// steps); factor entries are fetched a batch of steps at a time.
-template <int NT>
+// lost); `lc` holds the lower couplings staged by stage_lower (linear deflation), `scratch`
+// kChainScratch LDS entries.  `fac` is the handle's factor base (the subdomain offset is applied
+// here).  `before` forms the right-hand side in `t` (ending in a workgroup barrier); it runs with
+// the first factor blocks already on their way.
+template <int NT, int Kind, typename Before>
 __device__ __forceinline__ void coarse_solve(const SubDesc& d, const cplx<double>* __restrict__ fac,
-                                             const cplx<double>* lc, cplx<double>* t, cplx<double>* a) {
+                                             const cplx<double>* lc, cplx<double>* t, cplx<double>* a,
+                                             cplx<double>* scratch, Before before) {
   const cplx<double>* __restrict__ F = fac + d.goff;
-  if (d.defl != 0) {
-    detail::coarse_solve_paired<NT>(d, F, t, a);
-    return;
-  }
-  // the two halves run the two sweeps: 512 threads give 8 lanes per block row (mx <= 32),
-  // 256 threads 4 lanes; rings of 3 steps (a deeper ring makes the subdomain-solve kernel
-  // spill the ring's column offsets to scratch inside the step loop, where each reload
-  // waits for every factor load in flight)
-  auto lower = [lc, mx = d.mx](int i, int c, int e) { return lc[3 * (i * mx + c) + e]; };
-  if (d.mx <= 32) {
-    if constexpr (NT >= 512) detail::twisted_solve_ring<8, 4, 3, NT / 2>(d.mx, d.my, F, lower, t, a);
-    else detail::twisted_solve_ring<4, 8, 3, NT / 2>(d.mx, d.my, F, lower, t, a);
+  if constexpr (Kind == kCoarseNarrow) {
+    detail::CoarseChain<NT, 4, 4, 6> ch;
+    ch.start(d.mx, d.my, F);
+    before();
+    ch.solve(F, lc, t, a, scratch);
+  } else if constexpr (Kind == kCoarseChain) {
+    detail::CoarseChain<NT, 2, 13, 3> ch;
+    ch.start(d.mx, d.my, F);
+    before();
+    ch.solve(F, lc, t, a, scratch);
   } else {
-    detail::twisted_solve_plain<NT / 2>(d.mx, d.my, F, lower, t, a);
+    before();
+    if (d.defl != 0) {
+      detail::coarse_solve_paired<NT>(d, F, t, a);
+      return;
+    }
+    auto lower = [lc, mx = d.mx](int i, int c, int e) { return lc[3 * (i * mx + c) + e]; };
+    if (d.mx <= 32) {
+      if constexpr (NT >= 512) detail::twisted_solve_ring<8, 4, 3, NT / 2>(d.mx, d.my, F, lower, t, a);
+      else detail::twisted_solve_ring<4, 8, 3, NT / 2>(d.mx, d.my, F, lower, t, a);
+    } else {
+      detail::twisted_solve_plain<NT / 2>(d.mx, d.my, F, lower, t, a);
+    }
   }
 }
 

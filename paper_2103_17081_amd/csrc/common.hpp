@@ -85,11 +85,17 @@ struct SubDesc {
   int bmx, bmy;      // block factorisation of E: bmy block rows of bmx unknowns (linear: mx, my;
                      // Bezier: pairs of coarse rows, 2 mx and ceil(my / 2))
   int ncp;           // coarse vector length of the solve, bmx * bmy (>= mx * my)
-  int pad;
+  unsigned inv_nx;   // reciprocals for row_of: floor(2^32 / nx) + 1 and the same of mx
+  unsigned inv_mx;
   long long off;     // offset of the tile in packed fine vectors (elements)
   long long coff;    // offset in packed coarse vectors (elements)
   long long goff;    // offset of the coarse factors (complex<double> elements)
 };
+
+// n / width for width >= 2 from its reciprocal floor(2^32 / width) + 1 (exact while n width < 2^32;
+// n itself for width 1, whose reciprocal is stored as 0).
+inline unsigned row_reciprocal(int width) { return width > 1 ? (unsigned)((1ull << 32) / (unsigned)width) + 1u : 0u; }
+__device__ __forceinline__ int row_of(int n, unsigned inv) { return inv ? (int)__umulhi((unsigned)n, inv) : n; }
 
 // Problem-wide constants.
 struct Consts {
@@ -108,6 +114,15 @@ constexpr int kClasses = 9;        // (left edge | middle | right edge) x (botto
 // fence would drain), so loads issued ahead of the barrier stay in flight.
 __device__ __forceinline__ void lds_barrier() {
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
+// The thread index, opaque to the compiler at this point of the program: what is derived from it
+// (node coordinates, addresses) is then formed where it is used and not hoisted out of a long
+// loop, where it would occupy registers that the loop's largest phase needs.
+__device__ __forceinline__ int fresh_tid() {
+  int t = threadIdx.x;
+  asm volatile("" : "+v"(t));
+  return t;
 }
 
 // ---- wavefront / workgroup reductions ------------------------------------
@@ -159,6 +174,48 @@ __device__ __forceinline__ T wave_total(T v) {
   v += dpp<kDppBcast15, 0xA>(v);
   v += dpp<kDppBcast31, 0xC>(v);
   return v;
+}
+
+// wave_total's sum in every lane (uniform: read from the last lane).
+__device__ __forceinline__ double wave_total_all(double v) {
+  v = wave_total(v);
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_readlane((int)(b & 0xffffffffll), kWave - 1);
+  const int hi = __builtin_amdgcn_readlane((int)(b >> 32), kWave - 1);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+
+// (lanes 0..31 of a, lanes 0..31 of b) + (lanes 32..63 of a, lanes 32..63 of b), and the same
+// with alternate 16-lane rows: each adds two registers' halves in one addition.
+__device__ __forceinline__ float fold32(float a, float b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float fold16(float a, float b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ double join_f64(unsigned lo, unsigned hi) {
+  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+__device__ __forceinline__ double fold32(double a, double b) {
+  const unsigned long long x = (unsigned long long)__double_as_longlong(a), y = (unsigned long long)__double_as_longlong(b);
+  const auto l = __builtin_amdgcn_permlane32_swap((unsigned)x, (unsigned)y, false, false);
+  const auto h = __builtin_amdgcn_permlane32_swap((unsigned)(x >> 32), (unsigned)(y >> 32), false, false);
+  return join_f64(l[0], h[0]) + join_f64(l[1], h[1]);
+}
+__device__ __forceinline__ double fold16(double a, double b) {
+  const unsigned long long x = (unsigned long long)__double_as_longlong(a), y = (unsigned long long)__double_as_longlong(b);
+  const auto l = __builtin_amdgcn_permlane16_swap((unsigned)x, (unsigned)y, false, false);
+  const auto h = __builtin_amdgcn_permlane16_swap((unsigned)(x >> 32), (unsigned)(y >> 32), false, false);
+  return join_f64(l[0], h[0]) + join_f64(l[1], h[1]);
+}
+
+// Wave sums of four values at once: 16-lane row 0 gets the sum of a, row 1 of c, row 2 of b, row 3
+// of d, in every lane of the row.  Folding first leaves one row sum for the four.
+template <typename T>
+__device__ __forceinline__ T wave_totals4(T a, T b, T c, T d) {
+  return row_sum<16>(fold16(fold32(a, b), fold32(c, d)));
 }
 
 // Sum over the whole wavefront; every lane gets it.

@@ -45,7 +45,7 @@ struct InnerArgs {
   cplx<double>* R;               // per solve 2 maxit*maxit: the upper-triangular factor, then the
                                  // upper-triangular coordinates T of the Krylov candidates
   cplx<double>* Sc;              // per solve (maxit + 2) coarse vectors of max_nc: E^{-1} Z^T f, E^{-1} Z^T B x0,
-                                 // E^{-1} Z^T B u~_i (kept so that the recovery needs no coarse solve), or null
+                                 // E^{-1} Z^T B u~_i (kept so that the recovery needs no coarse solve)
   int* iters;                    // [nrhs][nsub] inner iterations, or null
   int* flags;                    // [nrhs][nsub] bit0 guess accepted, bit1 not converged
   const int* done;               // [nrhs] skip right-hand sides already converged, or null
@@ -58,6 +58,7 @@ struct InnerArgs {
   int nrhs, maxit, max_nj, max_nc;
   double tol;
   int nt;                        // threads per workgroup: 256 or 512 (autotuned)
+  int kind;                      // form of the coarse solve (CoarseKind of the widest subdomain)
 };
 
 template <typename T>

@@ -139,67 +139,44 @@ __global__ void __launch_bounds__(kBlock) factor_coarse_twisted_kernel(const Sub
     return (c - r >= -1 && c - r <= 1) ? ec[(size_t)(i * mx + r) * 9 + 1 + (c - r)] : czero<double>();
   };
   auto Uv = [&](int i, int r, int c) { return Lv(i + 1, c, r); };
-  auto blk = [&](int b) { return F + (size_t)b * mm; };
+  auto blk = [&](int i) { return F + (size_t)i * mm; };
+  // (L_i G_{i-1} U_{i-1})(r, c) and (U_i G_{i+1} L_{i+1})(r, c); element (r, c) of a block at c mx + r
+  auto from_below = [&](int i, int r, int c) {
+    const cplx<double>* G = blk(i - 1);
+    cplx<double> s = czero<double>();
+    for (int cc = max(c - 1, 0); cc <= min(c + 1, mx - 1); ++cc) {
+      cplx<double> h = czero<double>();
+      for (int rr = max(r - 1, 0); rr <= min(r + 1, mx - 1); ++rr) h = h + Lv(i, r, rr) * G[cc * mx + rr];
+      s = s + h * Uv(i - 1, cc, c);
+    }
+    return s;
+  };
+  auto from_above = [&](int i, int r, int c) {
+    const cplx<double>* G = blk(i + 1);
+    cplx<double> s = czero<double>();
+    for (int cc = max(c - 1, 0); cc <= min(c + 1, mx - 1); ++cc) {
+      cplx<double> h = czero<double>();
+      for (int rr = max(r - 1, 0); rr <= min(r + 1, mx - 1); ++rr) h = h + Uv(i, r, rr) * G[cc * mx + rr];
+      s = s + h * Lv(i + 1, cc, c);
+    }
+    return s;
+  };
   double minp = 1e300;
-  // top: G_i = (D_i - L_i H_{i-1})^{-1}, H_i = G_i U_i
-  for (int i = 0; i < p; ++i) {
-    cplx<double>* G = blk(tw_G(i));
+  // top rows upward, bottom rows downward, then the middle row.  A block is written
+  // transposed, so the in-place inverse leaves the transposed inverse.
+  for (int s = 0; s < my; ++s) {
+    const int i = s < p ? s : (s < my - 1 ? my - 1 - (s - p) : p);
+    cplx<double>* G = blk(i);
     for (int e = tid; e < mm; e += blockDim.x) {
-      const int r = e / mx, c = e - r * mx;
-      cplx<double> s = Dv(i, r, c);
-      if (i > 0) {
-        const cplx<double>* Hp = blk(tw_H(p, i - 1));
-        for (int rr = max(r - 1, 0); rr <= min(r + 1, mx - 1); ++rr) s = s - Lv(i, r, rr) * Hp[rr * mx + c];
-      }
-      G[e] = s;
+      const int c = e / mx, r = e - c * mx;
+      cplx<double> v = Dv(i, r, c);
+      if (i <= p && i > 0) v = v - from_below(i, r, c);
+      if (i >= p && i < my - 1) v = v - from_above(i, r, c);
+      G[e] = v;
     }
     __syncthreads();
     minp = fmin(minp, gauss_jordan_inverse(G, mx, perm, colp, &pivabs));
-    cplx<double>* H = blk(tw_H(p, i));
-    for (int e = tid; e < mm; e += blockDim.x) {
-      const int r = e / mx, c = e - r * mx;
-      cplx<double> s = czero<double>();
-      for (int cc = max(c - 1, 0); cc <= min(c + 1, mx - 1); ++cc) s = s + G[r * mx + cc] * Uv(i, cc, c);
-      H[e] = s;
-    }
-    __syncthreads();
   }
-  // bottom: K_i = (D_i - U_i J_{i+1})^{-1}, J_i = K_i L_i
-  for (int i = my - 1; i > p; --i) {
-    cplx<double>* K = blk(tw_K(p, i));
-    for (int e = tid; e < mm; e += blockDim.x) {
-      const int r = e / mx, c = e - r * mx;
-      cplx<double> s = Dv(i, r, c);
-      if (i < my - 1) {
-        const cplx<double>* Jn = blk(tw_J(my, i + 1));
-        for (int rr = max(r - 1, 0); rr <= min(r + 1, mx - 1); ++rr) s = s - Uv(i, r, rr) * Jn[rr * mx + c];
-      }
-      K[e] = s;
-    }
-    __syncthreads();
-    minp = fmin(minp, gauss_jordan_inverse(K, mx, perm, colp, &pivabs));
-    cplx<double>* J = blk(tw_J(my, i));
-    for (int e = tid; e < mm; e += blockDim.x) {
-      const int r = e / mx, c = e - r * mx;
-      cplx<double> s = czero<double>();
-      for (int cc = max(c - 1, 0); cc <= min(c + 1, mx - 1); ++cc) s = s + K[r * mx + cc] * Lv(i, cc, c);
-      J[e] = s;
-    }
-    __syncthreads();
-  }
-  // middle: M = (D_p - L_p H_{p-1} - U_p J_{p+1})^{-1}
-  cplx<double>* M = blk(tw_M(my));
-  for (int e = tid; e < mm; e += blockDim.x) {
-    const int r = e / mx, c = e - r * mx;
-    cplx<double> s = Dv(p, r, c);
-    for (int rr = max(r - 1, 0); rr <= min(r + 1, mx - 1); ++rr) {
-      if (p > 0) s = s - Lv(p, r, rr) * blk(tw_H(p, p - 1))[rr * mx + c];
-      if (p < my - 1) s = s - Uv(p, r, rr) * blk(tw_J(my, p + 1))[rr * mx + c];
-    }
-    M[e] = s;
-  }
-  __syncthreads();
-  minp = fmin(minp, gauss_jordan_inverse(M, mx, perm, colp, &pivabs));
   __shared__ double red[kBlock / kWave];
   const double emax = block_absmax(ec, (long long)mx * my * 9, red);
   if (tid == 0) {
