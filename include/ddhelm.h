@@ -91,7 +91,8 @@ typedef struct {
                           p_c = floor(c N / M + 1/2), c = 0..M; Z_0 = Z^y kron Z^x with the
                           piecewise-linear hats of the interior lines (the global analogue of the
                           linear deflation of eq. 5); E_0 = Z_0^T A Z_0 factored exactly (FP64
-                          block cyclic reduction); each application is
+                          nested dissection, or by block cyclic reduction below 8
+                          coarse intervals per wavelength); each application is
                           M^{-1} r = M_1^{-1} (r - A Q_0 r) + Q_0 r, Q_0 = Z_0 E_0^{-1} Z_0^T, with
                           M_1^{-1} the one-level preconditioner.  Needs M <= N and M - 1 <= 1024. */
   int inner_launch;    /* DD_INNER_FUSED (default): every subdomain solve of a preconditioner
@@ -147,7 +148,7 @@ typedef struct {
   double ms_coarse;            /* two-level coarse correction: restriction, coarse solve, Z_0 x and
                                   r - A Z_0 x (timed outer steps only; 0 for the one-level method) */
   double coarse_bytes;         /* factor and vector bytes one coarse solve reads and writes (the
-                                  algorithmic traffic of the block cyclic reduction); 0 without it */
+                                  algorithmic traffic of its solver); 0 without it */
 } dd_stats;
 
 /* Fill *p with the defaults: k = 20, ppwl = 10, 2 x 2 uniform subdomains, overlap 1,
@@ -259,13 +260,13 @@ dd_status dd_op_inner_solve_static(dd_handle* h, const void* f, void* u, int32_t
 int64_t dd_global_coarse_size(const dd_handle* h);
 /* Host copy of E_0 = Z_0^T A Z_0 (real: A has Dirichlet conditions on the whole boundary
    and Z_0 is real), 9 doubles per coarse unknown ((M-1)^2 of them, x fastest), neighbour
-   (cx+dx, cy+dy) at 3(dy+1) + (dx+1); and the smallest |pivot| met by the block
-   inversions of its cyclic reduction.  DD_EINVAL for a one-level handle. */
+   (cx+dx, cy+dy) at 3(dy+1) + (dx+1); and the smallest |pivot| met by the
+   elimination of its solver.  DD_EINVAL for a one-level handle. */
 dd_status dd_global_coarse_matrix(const dd_handle* h, double* out, double* min_pivot);
 /* t = Z_0^T r: global complex128 r [ndof] -> coarse complex128 t [(M-1)^2]; one
    right-hand side. */
 dd_status dd_op_global_restrict(dd_handle* h, const void* r, void* t, void* stream);
-/* y = E_0^{-1} t by the FP64 block cyclic reduction; coarse complex128 vectors. */
+/* y = E_0^{-1} t by the FP64 solver of the handle; coarse complex128 vectors. */
 dd_status dd_op_global_coarse_solve(dd_handle* h, const void* t, void* y, void* stream);
 /* q = Z_0 y and w = r - A q: the coarse correction and the residual the subdomain
    solves of the two-level preconditioner receive.  r, q, w global complex128 [ndof]

@@ -413,7 +413,7 @@ class Solver:
     # -- two-level method --
     def global_coarse_matrix(self):
         """E_0's coefficients ([(M-1)^2, 9] float64, neighbour (dx, dy) at 3(dy+1) + (dx+1)) and
-        the smallest |pivot| of its block cyclic reduction."""
+        the smallest |pivot| of its elimination."""
         out = np.zeros(self.nglobal_coarse * 9)
         piv = ctypes.c_double()
         _check(lib().dd_global_coarse_matrix(self._h, out.ctypes.data_as(ctypes.POINTER(ctypes.c_double)),

@@ -132,6 +132,7 @@ __device__ __forceinline__ int fresh_tid() {
 constexpr int kDppXor1 = 0xB1;          // quad_perm [1,0,3,2]
 constexpr int kDppXor2 = 0x4E;          // quad_perm [2,3,0,1]
 constexpr int kDppHalfMirror = 0x141;   // row_half_mirror
+constexpr int kDppRowRor8 = 0x128;      // row_ror:8 (the other half row)
 constexpr int kDppMirror = 0x140;       // row_mirror
 
 constexpr int kDppBcast15 = 0x142;      // row_bcast:15 (last lane of each row to the next row)

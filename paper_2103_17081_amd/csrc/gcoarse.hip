@@ -1,5 +1,6 @@
 // Global coarse space of the two-level method: Z_0, E_0 = Z_0^T A Z_0, its block
-// cyclic reduction and the coarse correction (definitions in gcoarse.hpp).
+// cyclic reduction and the coarse correction (definitions and the choice of the solver in
+// gcoarse.hpp).
 //
 // The global matrix A has homogeneous Dirichlet conditions on the boundary of the
 // unit square (Sec. 2, eqs. 1-2), so it is real; Z_0 is real, hence E_0 and all of its
@@ -507,6 +508,21 @@ hipError_t GlobalCoarse::setup(int n, int m, double k, int nr, hipStream_t st) {
   GC_TRY(alloc(&q, (size_t)nr * ndof));
   GC_TRY(alloc(&w, (size_t)nr * ndof));
 
+  if (2.0 * M_PI * m >= kNdIntervals * k) {
+    nd = std::make_unique<NestedDissection>();
+    GC_TRY(nd->setup(E0c, nc, nr, cv, st));
+    if (nd->accurate) {
+      min_pivot = nd->min_pivot;
+      solve_bytes_ = nd->solve_bytes;
+      std::vector<double> emax(kAbsMaxBlocks, 0.0);
+      GC_TRY(hipMemcpyAsync(emax.data(), emax_d, sizeof(double) * kAbsMaxBlocks, hipMemcpyDeviceToHost, st));
+      GC_TRY(hipStreamSynchronize(st));
+      max_entry = *std::max_element(emax.begin(), emax.end());
+      return hipSuccess;
+    }
+    nd.reset();
+  }
+
   // ---- plan the block cyclic reduction ----
   // Work blocks: B_i, A_i, C_i per block row, then the level-0 products Fm_i, Fp_i that
   // only the set-up needs.
@@ -759,6 +775,7 @@ hipError_t GlobalCoarse::restrict_rhs(const cplx<double>* r, long long rstride, 
 }
 
 hipError_t GlobalCoarse::solve(int nr, hipStream_t st) {
+  if (nd) return nd->solve(nr, st);
   for (const BcrPhase& ph : phases) {
     if (ph.kind == 1) {
       hipLaunchKernelGGL(gc_sparse_kernel, dim3((unsigned)((nc + 255) / 256), (unsigned)ph.count, (unsigned)nr),

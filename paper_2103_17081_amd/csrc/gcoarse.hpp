@@ -10,8 +10,18 @@
 //
 // with M_1^{-1} the one-level restricted Schwarz preconditioner of eq. 3.
 //
+// E_0 is solved exactly in FP64 by one of two methods.  Coarse grids of at least
+// kNdIntervals intervals per wavelength take the nested dissection of dissection.hpp: fewer bytes,
+// launches and set-up operations (n = M-1 = 317: 338 -> 109 us per solve, 139 -> 41 ms for the set-up;
+// n = 636: 1814 -> 294 us, 1353 -> 33 ms), and a relative error of 3e-12 at most, unless the set-up finds
+// k^2 too near an eigenvalue of one of its boxes.  On coarser ones the
+// reduction's rounding error, which k^2 near an eigenvalue of one of its pivots raises, shows in the
+// result: over 500 grids of up to 400 intervals the two methods' corrections differ by more
+// than 1e-9 on 5 of 234 at 10 intervals per wavelength and on 23 of 266 at 5.  Results there are held
+// to what they were, so the reduction stays.
+//
 // E_0 is block tridiagonal in the coarse rows (nb = M-1 blocks of n = M-1 unknowns).
-// It is solved exactly in FP64 by block cyclic reduction: at every level the odd
+// In the block cyclic reduction, at every level the odd
 // block rows of the remaining system are eliminated in terms of their even
 // neighbours, which halves the system, until one block row remains.  With the
 // inverse Binv_e of an eliminated row's diagonal block and its couplings A_e (lower)
@@ -31,14 +41,17 @@
 // GEMM and a batched Gauss-Jordan inverse with partial pivoting inside each block.
 #pragma once
 
+#include <memory>
 #include <vector>
 
 #include "common.hpp"
+#include "dissection.hpp"
 #include "outer.hpp"
 
 namespace ddh {
 
 constexpr int kMaxGlobalCoarse = 1024;  // largest coarse block n = M - 1
+constexpr double kNdIntervals = 8.0;    // coarse intervals per wavelength, nested dissection from here on
 constexpr int kBcrRhsGroup = 8;         // right-hand sides per pass of the solve kernel
 constexpr int kBcrTile = 64;            // rows per tile of the factors' solve layout
 
@@ -98,6 +111,7 @@ class GlobalCoarse {
   int* cell = nullptr;           // [N + 1] coarse interval containing each fine index
   double* E0c = nullptr;         // [ncoarse][9] coefficients, neighbour (dx, dy) at 3 (dy + 1) + (dx + 1)
   double* emax_d = nullptr;      // per-workgroup largest |coefficient| of E_0
+  std::unique_ptr<NestedDissection> nd;   // set: solves E_0 in place of the reduction
   double* fac = nullptr;         // block cyclic reduction factors (real: A and Z_0 are real)
   BcrTask* tasks = nullptr;
   SpTask* sptasks = nullptr;
@@ -115,7 +129,7 @@ class GlobalCoarse {
   // b = Z_0^T r into the b segments (r: rhs stride rstride, advanced by jdev * rslot).
   hipError_t restrict_rhs(const cplx<double>* r, long long rstride, const int* jdev, long long rslot,
                           const int* done, int nr, hipStream_t st);
-  // x = E_0^{-1} b (block cyclic reduction).
+  // x = E_0^{-1} b.
   hipError_t solve(int nr, hipStream_t st);
   // q = Z_0 x and w = r - A q.
   hipError_t correct(const cplx<double>* r, long long rstride, const int* jdev, long long rslot, const int* done,
