@@ -125,8 +125,9 @@ hipError_t launch_conv(const ConvArgs& a, int batch, hipStream_t st);
 size_t conv_lds_bytes(int H, int W, int cinp, int nb, int ksteps);
 hipError_t launch_conv_wgrad(const ConvArgs& a, const bf16* dz, int cout, int batch, float* part, float* bpart,
                              hipStream_t st);
-size_t wgrad_lds_bytes(int H, int W, int cinp, int cout);
-hipError_t launch_wgrad_reduce(const float* part, const float* bpart, int batch, int cin, int cinp, int cout,
+// Partials that launch_conv_wgrad writes (rows of part and bpart); grows with the batch.
+int wgrad_partials(int H, int W, int cinp, int cout, int batch);
+hipError_t launch_wgrad_reduce(const float* part, const float* bpart, int groups, int cin, int cinp, int cout,
                                int taps, float* gW, float* gb, hipStream_t st);
 hipError_t launch_route(const RouteArgs& a, hipStream_t st);
 hipError_t launch_head(const HeadArgs& a, hipStream_t st);

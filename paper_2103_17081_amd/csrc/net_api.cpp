@@ -128,7 +128,8 @@ dd_status backward(dd_net* n, int batch, hipStream_t st) {
     const ddh::NetLayer& L = nt.l[i];
     ddh::ConvArgs a = layer_args(n, i);
     NET_HIP(ddh::launch_conv_wgrad(a, n->dz[i], L.cout, batch, n->part, n->bpart, st));
-    NET_HIP(ddh::launch_wgrad_reduce(n->part, n->bpart, batch, L.cin, L.cinp, L.cout, 9, n->grads + L.woff,
+    const int groups = ddh::wgrad_partials(a.H, a.W, a.cinp, L.cout, batch);
+    NET_HIP(ddh::launch_wgrad_reduce(n->part, n->bpart, groups, L.cin, L.cinp, L.cout, 9, n->grads + L.woff,
                                      n->grads + L.boff, st));
     if (i == 0) break;
     // data gradient at the layer input: the same product with flipped weights
@@ -272,19 +273,21 @@ dd_status dd_net_create(const dd_net_params* p, dd_net** out) {
     NET_A(n->grads, (size_t)n->nparams);
     NET_A(n->m, (size_t)n->nparams);
     NET_A(n->v, (size_t)n->nparams);
-    size_t part = 2 * (size_t)n->nt.c1;
+    size_t part = B * 2 * (size_t)n->nt.c1, bpart = B * 2;   // the head's, one per tile
     for (int i = 0; i < ddh::kNetConv; ++i) {
       const ddh::NetLayer& L = n->nt.l[i];
       const int H = n->H(L.level);
       NET_A(n->dz[i], B * H * H * L.cout);
       if (i > 0) NET_A(n->dc[i], B * H * H * L.cin);
-      part = std::max(part, (size_t)9 * L.cinp * L.cout);
+      const size_t groups = ddh::wgrad_partials(H, H, L.cinp, L.cout, n->B);
+      part = std::max(part, groups * 9 * L.cinp * L.cout);
+      bpart = std::max(bpart, groups * L.cout);
     }
     NET_A(n->E, B * T2 * 2);
     NET_A(n->R, B * T2 * 2);
     NET_A(n->t, B * T2 * 2);
-    NET_A(n->part, B * part);
-    NET_A(n->bpart, B * 64);
+    NET_A(n->part, part);
+    NET_A(n->bpart, bpart);
     NET_A(n->loss, B);
     NET_A(n->desc, B);
   }
