@@ -35,8 +35,9 @@ constexpr int kNetInP = 8;
 constexpr int kNetOut = 2;
 constexpr int kNetConv = 7;          // 3x3 layers; the 1x1 head follows
 constexpr int kNetThreads = 256;
+constexpr int kConvSteps = 3;        // steps whose weight fragments a wave holds
 
-enum ConvMode { kPlain = 0, kPool = 1, kUpCat = 2 };
+enum ConvMode { kPlain = 0, kPool = 1, kUpCat = 2, kInput = 3 };
 
 struct NetLayer {
   int cin, cinp, cout;   // input channels (real / stored), output channels
@@ -45,7 +46,7 @@ struct NetLayer {
   int src0, src1;        // activation index of the operands (-1: network input)
   long long woff, boff;  // parameter offsets (floats)
   long long ffrag, bfrag;  // offsets (bf16x8 units) of forward / data-gradient fragments
-  int ksteps, bksteps;   // 32-wide k steps: forward 9 cinp, data gradient 9 cout
+  int ksteps, bksteps;   // 32-wide k steps: forward 9 cinp, data gradient 9 cout, rounded up to kConvSteps
 };
 
 struct NetTable {
@@ -66,11 +67,14 @@ struct TileDescDev {
 struct ConvArgs {
   const bf16* x0;        // kPlain: input [B][H][W][cinp]; kPool: [B][2H][2W][cinp]; kUpCat: [B][H/2][W/2][c1]
   const bf16* x1;        // kUpCat: skip operand [B][H][W][cinp - c1]
+  const float* xf;       // kInput: the caller's network input [B][H][W][4], rounded while it is staged
   const bf16x8* wf;      // weight fragments [ksteps][NB][64 lanes]
   const float* bias;     // [NB*16] or null
   bf16* out_bf;          // [B][H][W][NB*16] (bf16) or null
   float* out_f;          // [B][H][W][NB*16] (fp32) or null
-  int H, W, lw;          // lw = log2(W)
+  float* y;              // [B][H][W][2]: apply the head instead of storing the output, or null
+  const float* head;     // with y: weights [NB*16][2], then the biases
+  int H, W, lw, lc;      // lw = log2(W), lc = log2(cinp)
   int cinp, c1, mode, relu, ksteps, nb;
 };
 
@@ -93,8 +97,7 @@ struct HeadArgs {
   long long woff, boff;
   int c1, T;
   float* y;              // [B][T][T][2]
-  // training
-  const float* t;        // targets [B][T][T][2] or null (inference)
+  const float* t;        // targets [B][T][T][2]
   const TileDescDev* desc;
   double w_res, w_err;
   int batch;
@@ -122,7 +125,6 @@ struct TileArgs {
 
 hipError_t launch_net_prepare(const NetTable& nt, const float* params, bf16x8* frags, hipStream_t st);
 hipError_t launch_conv(const ConvArgs& a, int batch, hipStream_t st);
-size_t conv_lds_bytes(int H, int W, int cinp, int nb, int ksteps);
 hipError_t launch_conv_wgrad(const ConvArgs& a, const bf16* dz, int cout, int batch, float* part, float* bpart,
                              hipStream_t st);
 // Partials that launch_conv_wgrad writes (rows of part and bpart); grows with the batch.

@@ -45,6 +45,11 @@ dd_status net_alloc(dd_net* n, T** ptr, size_t count) {
   return DD_OK;
 }
 
+int conv_steps(int channels) {
+  const int steps = (9 * channels + 31) / 32;
+  return (steps + ddh::kConvSteps - 1) / ddh::kConvSteps * ddh::kConvSteps;
+}
+
 int log2i(int v) {
   int l = 0;
   while ((1 << l) < v) ++l;
@@ -79,8 +84,8 @@ void build_table(dd_net* n) {
     po += 9LL * L.cin * L.cout;
     L.boff = po;
     po += L.cout;
-    L.ksteps = (9 * L.cinp + 31) / 32;
-    L.bksteps = (9 * L.cout + 31) / 32;
+    L.ksteps = conv_steps(L.cinp);
+    L.bksteps = conv_steps(L.cout);
     L.ffrag = fo;
     fo += (long long)L.ksteps * (L.cout / 16) * 64;
     L.bfrag = fo;
@@ -106,6 +111,7 @@ ddh::ConvArgs layer_args(const dd_net* n, int i) {
   a.H = a.W = n->H(L.level);
   a.lw = log2i(a.W);
   a.cinp = L.cinp;
+  a.lc = log2i(a.cinp);
   a.c1 = L.c1;
   a.mode = L.mode;
   a.relu = 1;
@@ -140,6 +146,7 @@ dd_status backward(dd_net* n, int batch, hipStream_t st) {
     d.H = d.W = n->H(L.level);
     d.lw = log2i(d.W);
     d.cinp = L.cout;
+    d.lc = log2i(d.cinp);
     d.mode = ddh::kPlain;
     d.relu = 0;
     d.ksteps = L.bksteps;
@@ -186,23 +193,20 @@ void dd_net::release() {
 
 namespace ddh {
 
-dd_status net_forward(dd_net* n, int batch, hipStream_t st, bool head) {
+dd_status net_forward(dd_net* n, int batch, hipStream_t st, const float* xf, float* y) {
   for (int i = 0; i < kNetConv; ++i) {
     ConvArgs a = layer_args(n, i);
     a.out_bf = n->act[i];
+    if (i == 0 && xf) {
+      a.mode = kInput;
+      a.xf = xf;
+    }
+    if (i == kNetConv - 1 && y) {
+      a.y = y;
+      a.head = n->params + n->nt.hwoff;   // the biases follow the weights
+    }
     NET_HIP(launch_conv(a, batch, st));
   }
-  if (!head) return DD_OK;
-  HeadArgs h{};
-  h.a7 = n->act[kNetConv - 1];
-  h.params = n->params;
-  h.woff = n->nt.hwoff;
-  h.boff = n->nt.hboff;
-  h.c1 = n->nt.c1;
-  h.T = n->T;
-  h.y = n->y;
-  h.batch = batch;
-  NET_HIP(launch_head(h, st));
   return DD_OK;
 }
 
@@ -213,7 +217,7 @@ dd_status net_infer_from(dd_net* n, const TileArgs& ta0, int nsub, int nrhs, hip
   ta.xf = nullptr;
   ta.scale = n->scale;
   NET_HIP(launch_tiles(ta, nsub, nrhs, st));
-  return net_forward(n, nsub * nrhs, st);
+  return net_forward(n, nsub * nrhs, st, nullptr, n->y);
 }
 
 }  // namespace ddh
@@ -443,11 +447,7 @@ dd_status dd_net_forward(dd_net* n, const float* x, int batch, float* y, void* s
   if (!n || !x || !y) return ddh::fail_msg(DD_EINVAL, "null argument");
   if (batch < 1 || batch > n->B) return ddh::fail_msg(DD_EINVAL, "batch out of range");
   hipStream_t st = (hipStream_t)stream;
-  const long long pix = (long long)batch * n->T * n->T;
-  NET_HIP(ddh::launch_input_convert(x, n->x, pix, st));
-  NET_TRY(ddh::net_forward(n, batch, st));
-  NET_HIP(hipMemcpyAsync(y, n->y, (size_t)pix * 2 * sizeof(float), hipMemcpyDeviceToDevice, st));
-  return DD_OK;
+  return ddh::net_forward(n, batch, st, x, y);
 }
 
 dd_status dd_net_gradient(dd_net* n, const float* x, const float* t, const dd_tile_desc* desc, int batch,
@@ -464,7 +464,7 @@ dd_status dd_net_gradient(dd_net* n, const float* x, const float* t, const dd_ti
   const long long pix = (long long)batch * n->T * n->T;
   NET_HIP(hipMemcpyAsync(n->desc, desc, (size_t)batch * sizeof(dd_tile_desc), hipMemcpyHostToDevice, st));
   NET_HIP(ddh::launch_input_convert(x, n->x, pix, st));
-  NET_TRY(ddh::net_forward(n, batch, st, false));
+  NET_TRY(ddh::net_forward(n, batch, st, nullptr, nullptr));
   ddh::HeadArgs h{};
   h.a7 = n->act[ddh::kNetConv - 1];
   h.params = n->params;

@@ -44,7 +44,8 @@ namespace ddh {
 // Network input tiles of the solves of one preconditioner application, the forward
 // pass, and the guess tiles in net->y (all on `st`).
 dd_status net_infer_from(dd_net* net, const TileArgs& ta, int nsub, int nrhs, hipStream_t st);
-// The forward pass on net->x for `batch` tiles, output in net->y.
-dd_status net_forward(dd_net* net, int batch, hipStream_t st, bool head = true);
+// The forward pass for `batch` tiles on xf (fp32, 4 channels) or, where that is null, on net->x: the output
+// in y, or where that is null the head's input in net->act.
+dd_status net_forward(dd_net* net, int batch, hipStream_t st, const float* xf, float* y);
 
 }  // namespace ddh

@@ -57,75 +57,156 @@ __device__ __forceinline__ bf16x8 load_input(const ConvArgs& a, int b, int y, in
   return *(const bf16x8*)(a.x1 + (((size_t)b * H + y) * W + x) * cs + (ch - a.c1));
 }
 
-constexpr int kStageBatch = 8;   // staging loads each thread keeps in flight
+// 16 bytes at a 32-bit byte offset from a uniform base.
+template <typename V>
+__device__ __forceinline__ V load_at(const void* base, int bytes) {
+  return *(const V*)((const char*)base + (unsigned)bytes);
+}
 
-// Rows y0-1 .. y0+rows of tile b, columns -1 .. W, into LDS (pixel stride cinp + 8).
-// Each thread issues kStageBatch loads before storing any, so the band arrives in a few
-// memory latencies rather than one per unit.
-__device__ __forceinline__ void stage_input(const ConvArgs& a, int b, int y0, int rows, bf16* lds) {
-  const int W = a.W, cg = a.cinp >> 3, ps = a.cinp + 8, W2 = W + 2;
-  const int units = (rows + 2) * W2 * cg;
-  const int nt = blockDim.x;
-  for (int u0 = threadIdx.x; u0 < units; u0 += nt * kStageBatch) {
-    bf16x8 v[kStageBatch];
+// 2^lcg groups of 8 channels of rows y0-1 .. y0+rows of a tile into LDS, columns 0 .. W-1, from channel c0
+// (pixel stride ps, one pixel of halo on the left). The pixels of a band follow each other in memory, so a unit's
+// place is its number: the address takes a shift, and pixel p of the band goes to LDS pixel
+// p + 2 (p / W) + 1. Each thread issues its loads before it combines and stores any. Rows
+// outside the tile are read at its first or last pixel and stored as zeros.
+template <int MODE>
+__device__ __forceinline__ void stage_rows(const ConvArgs& a, const void* src, int lcg, int y0, int rows, int ps,
+                                           bf16* lds) {
+  constexpr int kBatch = MODE == kPool ? 4 : 8, kLoads = MODE == kPool ? 4 : 1, nt = kNetThreads;
+  const int n = (rows + 2) << a.lw << lcg, first = (y0 - 1) << a.lw, npix = a.H << a.lw;
+  for (int u0 = 0; u0 < n; u0 += nt * kBatch) {
+    bf16x8 v[kBatch][kLoads];
+    f32x4 f[kBatch];
 #pragma unroll
-    for (int q = 0; q < kStageBatch; ++q) {
-      const int u = u0 + q * nt;
-      v[q] = zero8();
-      if (u < units) {
-        const int g = u % cg, pc = u / cg;
-        const int c = pc % W2, r = pc / W2;
-        const int y = y0 - 1 + r, x = c - 1;
-        if (y >= 0 && y < a.H && x >= 0 && x < W) v[q] = load_input(a, b, y, x, g * 8);
+    for (int q = 0; q < kBatch; ++q) {
+      if (u0 + q * nt < n) {
+        const int e = u0 + q * nt + threadIdx.x, g = e & ((1 << lcg) - 1);
+        const int p = min(max(first + (e >> lcg), 0), npix - 1);
+        if (MODE == kInput) {
+          f[q] = load_at<f32x4>(src, p * 16);
+        } else if (MODE == kPool) {
+          const int at = (((4 * p - 2 * (p & (a.W - 1))) << lcg) + g) * 16;
+          const int right = 16 << lcg, down = right << (a.lw + 1);
+          v[q][0] = load_at<bf16x8>(src, at);
+          v[q][kLoads > 1 ? 1 : 0] = load_at<bf16x8>(src, at + right);
+          v[q][kLoads > 2 ? 2 : 0] = load_at<bf16x8>(src, at + down);
+          v[q][kLoads > 3 ? 3 : 0] = load_at<bf16x8>(src, at + down + right);
+        } else {
+          v[q][0] = load_at<bf16x8>(src, ((p << lcg) + g) * 16);
+        }
       }
     }
 #pragma unroll
-    for (int q = 0; q < kStageBatch; ++q) {
-      const int u = u0 + q * nt;
-      if (u < units) {
-        const int g = u % cg, pc = u / cg;
-        *(bf16x8*)(lds + (size_t)pc * ps + g * 8) = v[q];
+    for (int q = 0; q < kBatch; ++q) {
+      if (u0 + q * nt < n) {
+        const int e = u0 + q * nt + threadIdx.x, g = e & ((1 << lcg) - 1), p = e >> lcg;
+        bf16x8 o = zero8();
+        if (MODE == kInput) {
+#pragma unroll
+          for (int i = 0; i < kNetIn; ++i) o[i] = (bf16)f[q][i];
+        } else if (MODE == kPool) {
+#pragma unroll
+          for (int i = 0; i < 8; ++i)
+            o[i] = (bf16)(0.25f * (((float)v[q][0][i] + (float)v[q][kLoads > 1 ? 1 : 0][i]) +
+                                   ((float)v[q][kLoads > 2 ? 2 : 0][i] + (float)v[q][kLoads > 3 ? 3 : 0][i])));
+        } else {
+          o = v[q][0];
+        }
+        if ((unsigned)(first + p) >= (unsigned)npix) o = zero8();
+        if (e < n) *(bf16x8*)(lds + (p + 2 * (p >> a.lw) + 1) * ps + g * 8) = o;
       }
     }
   }
 }
 
-// n bf16x8 values from global to LDS, kStageBatch loads in flight per thread.
-__device__ __forceinline__ void stage_copy(const bf16x8* __restrict__ src, bf16x8* dst, int n) {
-  const int nt = blockDim.x;
-  for (int u0 = threadIdx.x; u0 < n; u0 += nt * kStageBatch) {
-    bf16x8 v[kStageBatch];
+// The same from a tile of half the resolution: each pixel is read once and stored to the up to four
+// that it covers.
+__device__ __forceinline__ void stage_upsampled(const ConvArgs& a, const void* src, int lcg, int y0, int rows, int ps,
+                                                bf16* lds) {
+  constexpr int kBatch = 4, nt = kNetThreads;
+  const int lwc = a.lw - 1, npix = (a.H >> 1) << lwc;
+  const int top = (y0 - 1) >> 1, first = top * (1 << lwc);   // y0 = 0: row -1
+  const int n = (((y0 + rows) >> 1) - top + 1) << lwc << lcg;
+  for (int u0 = 0; u0 < n; u0 += nt * kBatch) {
+    bf16x8 v[kBatch];
 #pragma unroll
-    for (int q = 0; q < kStageBatch; ++q) v[q] = u0 + q * nt < n ? src[u0 + q * nt] : zero8();
+    for (int q = 0; q < kBatch; ++q) {
+      if (u0 + q * nt < n) {
+        const int e = u0 + q * nt + threadIdx.x, g = e & ((1 << lcg) - 1);
+        const int p = min(max(first + (e >> lcg), 0), npix - 1);
+        v[q] = load_at<bf16x8>(src, ((p << lcg) + g) * 16);
+      }
+    }
 #pragma unroll
-    for (int q = 0; q < kStageBatch; ++q)
-      if (u0 + q * nt < n) dst[u0 + q * nt] = v[q];
+    for (int q = 0; q < kBatch; ++q) {
+      if (u0 + q * nt < n) {
+        const int e = u0 + q * nt + threadIdx.x, g = e & ((1 << lcg) - 1), p = e >> lcg;
+        bf16x8 o = v[q];
+        if ((unsigned)(first + p) >= (unsigned)npix) o = zero8();
+        const int x = p & ((1 << lwc) - 1), r = 2 * (top + (p >> lwc)) - (y0 - 1);   // band row of the upper two
+        bf16* d = lds + (r * (a.W + 2) + 2 * x + 1) * ps + g * 8;
+        if (e < n && r >= 0) {
+          *(bf16x8*)d = o;
+          *(bf16x8*)(d + ps) = o;
+        }
+        if (e < n && r + 1 < rows + 2) {
+          *(bf16x8*)(d + (a.W + 2) * ps) = o;
+          *(bf16x8*)(d + (a.W + 3) * ps) = o;
+        }
+      }
+    }
+  }
+}
+
+// Rows y0-1 .. y0+rows of the layer input, columns -1 .. W, into LDS (pixel stride cinp + 8 channels).
+__device__ __forceinline__ void stage_input(const ConvArgs& a, int b, int y0, int rows, bf16* lds) {
+  const int ps = a.cinp + 8, lcg = a.lc - 3;
+  const size_t pix = (size_t)b * a.H * a.W;
+  for (int u = threadIdx.x; u < (rows + 2) << (lcg + 1); u += kNetThreads) {
+    const int g = u & ((1 << lcg) - 1), e = u >> lcg;
+    *(bf16x8*)(lds + ((e >> 1) * (a.W + 2) + (e & 1) * (a.W + 1)) * ps + g * 8) = zero8();
+  }
+  switch (a.mode) {
+    case kPlain: stage_rows<kPlain>(a, a.x0 + pix * a.cinp, lcg, y0, rows, ps, lds); break;
+    case kPool: stage_rows<kPool>(a, a.x0 + 4 * pix * a.cinp, lcg, y0, rows, ps, lds); break;
+    case kInput: stage_rows<kInput>(a, a.xf + pix * kNetIn, lcg, y0, rows, ps, lds); break;
+    default:   // both operands have half of the channels
+      stage_upsampled(a, a.x0 + (pix >> 2) * a.c1, lcg - 1, y0, rows, ps, lds);
+      stage_rows<kPlain>(a, a.x1 + pix * a.c1, lcg - 1, y0, rows, ps, lds + a.c1);
   }
 }
 
 }  // namespace
 
-// LDS of one 3x3 product with MF fragments per wave: the staged input band (rounded up
-// to 16 bytes) followed by all weight fragments of the layer.
-static size_t conv_lds_bytes_mf(int H, int W, int cinp, int nb, int ksteps, int mf) {
+// LDS of one workgroup of a 3x3 product with MF fragments per wave: the staged band.
+static size_t conv_lds_bytes(int H, int W, int cinp, int mf) {
   const int np = std::min(64 * mf, H * W);
-  const int rows = (np + W - 1) / W;
-  const size_t in = ((size_t)(rows + 2) * (W + 2) * (cinp + 8) * sizeof(bf16) + 15) & ~size_t(15);
-  return in + (size_t)ksteps * nb * 64 * sizeof(bf16x8);
+  return (size_t)((np + W - 1) / W + 2) * (W + 2) * (cinp + 8) * sizeof(bf16);
 }
 
-// Fragments per wave: 4 unless that band plus the weights exceed the LDS.
-static int conv_mf(int H, int W, int cinp, int nb, int ksteps) {
-  if (nb >= 8) return 2;
-  return conv_lds_bytes_mf(H, W, cinp, nb, ksteps, 4) <= 160 * 1024 ? 4 : 2;
-}
-
-size_t conv_lds_bytes(int H, int W, int cinp, int nb, int ksteps) {
-  return conv_lds_bytes_mf(H, W, cinp, nb, ksteps, conv_mf(H, W, cinp, nb, ksteps));
+// Fragments per wave. More of them read fewer halo rows and weights; fewer give a small
+// batch more workgroups, each with less to stage before its first product. Two workgroups per compute
+// unit are enough (against four: 256 tiles of 64 x 64 108 and 112 us, 4 of 128 x 128 43 and
+// 49, one and 8 of 64 x 64 equal), and more than 80 KB of LDS would leave one.
+static int conv_mf(int H, int W, int cinp, int nb, int batch) {
+  int mf = nb >= 8 ? 2 : 4;
+  while (mf > 1 && ((long long)batch * ((H * W + 64 * mf - 1) / (64 * mf)) < 512 ||
+                    conv_lds_bytes(H, W, cinp, mf) > 80 * 1024))
+    mf >>= 1;
+  return mf;
 }
 
 // out[p][co] = bias[co] + sum_{tap, ci} in[p + off(tap)][ci] W[tap][ci][co]   (+ relu)
 // Grid: (ceil(H W / (64 MF)), batch); 256 threads; wave w owns fragments w + 4 f.
+//
+// The weight fragments go from L2 straight to registers, kConvSteps steps ahead, the first
+// before the band is staged: every wave needs all of them once, so LDS would only add a
+// copy, a wait and up to 72 KB. Bound by vector instructions (staging, addresses, rounding) and
+// the staging's latency; the matrix cores work a tenth of the time.
+// Forward pass at widths 16/32/64/64 with weights in LDS and the head, input rounding and
+// output copy in launches of their own: 217 us for 256 tiles of 64 x 64 and 113 for one, now 108 and 33.
+//
+// With a.y the 1x1 head follows in the same lanes, on the activations as rounded to bfloat16:
+// y[p] = out[p] W8 + b8, and out itself is not stored.
 template <int NB, int MF>
 __global__ void __launch_bounds__(kNetThreads) conv3x3_kernel(ConvArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
@@ -135,91 +216,155 @@ __global__ void __launch_bounds__(kNetThreads) conv3x3_kernel(ConvArgs a) {
   const int p0 = blockIdx.x * (64 * MF);
   const int np = min(64 * MF, npix - p0);
   const int y0 = p0 >> a.lw, rows = ((p0 + np - 1) >> a.lw) - y0 + 1;
-  stage_input(a, b, y0, rows, lds);
-  // all weight fragments of the layer, after the input band (whose LDS size is that of
-  // the first block, the largest)
-  const int rows0 = (min(64 * MF, npix) + W - 1) / W;
-  bf16x8* lwf = (bf16x8*)(smem + ((((size_t)(rows0 + 2) * (W + 2) * (a.cinp + 8) * sizeof(bf16)) + 15) & ~size_t(15)));
-  stage_copy(a.wf, lwf, a.ksteps * NB * 64);
-  __syncthreads();
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lr = lane & 15, lg = lane >> 4;
-  const int ps = a.cinp + 8, W2 = W + 2;
+  bf16x8 wv[kConvSteps][NB];
+#pragma unroll
+  for (int q = 0; q < kConvSteps; ++q)
+#pragma unroll
+    for (int n = 0; n < NB; ++n) wv[q][n] = load_at<bf16x8>(a.wf + (q * NB + n) * 64, lane * 16);
+  stage_input(a, b, y0, rows, lds);
+  __syncthreads();
+  const int ps = a.cinp + 8, W2 = W + 2, steps = a.ksteps;
   f32x4 acc[MF][NB];
-  int pofs[MF];
+  const bf16* at[MF];
 #pragma unroll
   for (int f = 0; f < MF; ++f) {
 #pragma unroll
     for (int n = 0; n < NB; ++n) acc[f][n] = f32x4{0.f, 0.f, 0.f, 0.f};
     const int p = p0 + (wave + 4 * f) * 16 + lr;
     const int py = p >> a.lw, px = p & (W - 1);
-    pofs[f] = ((py - y0 + 1) * W2 + px + 1) * ps;
+    // the top left tap; a fragment beyond the tile reads the band's first pixel
+    at[f] = lds + ((wave + 4 * f) * 16 < np ? (py - y0) * W2 + px : 0) * ps;
   }
-  for (int ks = 0; ks < a.ksteps; ++ks) {
-    const int k0 = ks * 32 + lg * 8;
-    const int tap = k0 / a.cinp, ch = k0 - tap * a.cinp;
-    const bool tv = tap < 9;
-    const int toff = tv ? ((tap / 3 - 1) * W2 + (tap % 3 - 1)) * ps + ch : 0;
-    bf16x8 wv[NB];
+  // Step ks from the fragments in wv[q], whose place the fragments of step ks + kConvSteps take.
+  const auto product = [&](int q, int ks, const bf16x8* xv) {
 #pragma unroll
-    for (int n = 0; n < NB; ++n) wv[n] = lwf[(ks * NB + n) * 64 + lane];
+    for (int f = 0; f < MF; ++f)
 #pragma unroll
-    for (int f = 0; f < MF; ++f) {
-      if ((wave + 4 * f) * 16 < np) {
-        const bf16x8 xv = tv ? *(const bf16x8*)(lds + pofs[f] + toff) : zero8();
+      for (int n = 0; n < NB; ++n) acc[f][n] = mfma(wv[q][n], xv[f], acc[f][n]);
+    const bf16x8* next = a.wf + (size_t)min(ks + kConvSteps, steps - 1) * (NB * 64);
 #pragma unroll
-        for (int n = 0; n < NB; ++n) acc[f][n] = mfma(wv[n], xv, acc[f][n]);
+    for (int n = 0; n < NB; ++n) wv[q][n] = load_at<bf16x8>(next + n * 64, lane * 16);
+  };
+  bf16x8 xv[MF];
+  if (a.lc >= 5) {
+    // 32 input channels or more: a step lies within one tap, the same for all lanes
+#pragma unroll
+    for (int f = 0; f < MF; ++f) at[f] += 8 * lg;
+    for (int ks0 = 0; ks0 < steps; ks0 += kConvSteps) {
+#pragma unroll
+      for (int q = 0; q < kConvSteps; ++q) {
+        const int k0 = (ks0 + q) * 32, tap = k0 >> a.lc, ty = (tap * 11) >> 5;
+        const int toff = (ty * W2 + tap - 3 * ty) * ps + (k0 & (a.cinp - 1));
+#pragma unroll
+        for (int f = 0; f < MF; ++f) xv[f] = *(const bf16x8*)(at[f] + toff);
+        product(q, ks0 + q, xv);
+      }
+    }
+  } else {
+    for (int ks0 = 0; ks0 < steps; ks0 += kConvSteps) {
+#pragma unroll
+      for (int q = 0; q < kConvSteps; ++q) {
+        const int k0 = (ks0 + q) * 32 + lg * 8, tap = k0 >> a.lc, ty = (tap * 11) >> 5, ch = k0 & (a.cinp - 1);
+        const int toff = (ty * W2 + tap - 3 * ty) * ps + ch;
+        // beyond the last tap (zero weights): the first row's left halo, which is zero
+#pragma unroll
+        for (int f = 0; f < MF; ++f) xv[f] = *(const bf16x8*)(tap < 9 ? at[f] + toff : lds + ch);
+        product(q, ks0 + q, xv);
       }
     }
   }
   constexpr int C = NB * 16;
+  f32x4 bias[NB];
+#pragma unroll
+  for (int n = 0; n < NB; ++n) {
+    bias[n] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (a.bias)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) bias[n][i] = a.bias[n * 16 + 4 * lg + i];
+  }
+  const size_t pb = (size_t)b * npix + p0 + wave * 16 + lr;
+  if (a.y) {
+    float hw[NB][4][2];
+#pragma unroll
+    for (int n = 0; n < NB; ++n)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        hw[n][i][0] = a.head[2 * (n * 16 + 4 * lg + i)];
+        hw[n][i][1] = a.head[2 * (n * 16 + 4 * lg + i) + 1];
+      }
+    const float hb = a.head[2 * C + (lg & 1)];
+#pragma unroll
+    for (int f = 0; f < MF; ++f) {
+      float h0 = 0.0f, h1 = 0.0f;
+#pragma unroll
+      for (int n = 0; n < NB; ++n)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const float o = acc[f][n][i] + bias[n][i];
+          const float v = (float)(bf16)(a.relu ? fmaxf(o, 0.0f) : o);
+          h0 = fmaf(v, hw[n][i][0], h0);
+          h1 = fmaf(v, hw[n][i][1], h1);
+        }
+      // lanes lr, lr + 16, lr + 32, lr + 48 hold the pixel's channels
+#pragma unroll
+      for (int m = 16; m < kWave; m <<= 1) {
+        h0 += __shfl_xor(h0, m, kWave);
+        h1 += __shfl_xor(h1, m, kWave);
+      }
+      if (lg < 2 && (wave + 4 * f) * 16 < np) a.y[2 * (pb + 64 * f) + lg] = (lg ? h1 : h0) + hb;
+    }
+    return;
+  }
 #pragma unroll
   for (int f = 0; f < MF; ++f) {
     if ((wave + 4 * f) * 16 >= np) continue;
-    const size_t p = (size_t)b * npix + p0 + (wave + 4 * f) * 16 + lr;
 #pragma unroll
     for (int n = 0; n < NB; ++n) {
-      const int co = n * 16 + 4 * lg;
-      float o[4];
+      const size_t o = (pb + 64 * f) * C + n * 16 + 4 * lg;
+      f32x4 v = acc[f][n] + bias[n];
+      if (a.relu)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        o[i] = acc[f][n][i] + (a.bias ? a.bias[co + i] : 0.0f);
-        if (a.relu) o[i] = fmaxf(o[i], 0.0f);
-      }
+        for (int i = 0; i < 4; ++i) v[i] = fmaxf(v[i], 0.0f);
       if (a.out_bf) {
-        bf16x4 v;
+        bf16x4 r;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) v[i] = (bf16)o[i];
-        *(bf16x4*)(a.out_bf + p * C + co) = v;
+        for (int i = 0; i < 4; ++i) r[i] = (bf16)v[i];
+        *(bf16x4*)(a.out_bf + o) = r;
       } else {
-        *(f32x4*)(a.out_f + p * C + co) = f32x4{o[0], o[1], o[2], o[3]};
+        *(f32x4*)(a.out_f + o) = v;
       }
     }
   }
 }
 
-hipError_t launch_conv(const ConvArgs& a, int batch, hipStream_t st) {
-  const int npix = a.H * a.W;
-  const int mf = conv_mf(a.H, a.W, a.cinp, a.nb, a.ksteps);
-  const dim3 grid((npix + 64 * mf - 1) / (64 * mf), batch);
-  const size_t lds = conv_lds_bytes_mf(a.H, a.W, a.cinp, a.nb, a.ksteps, mf);
-  if (lds > 160 * 1024) return hipErrorInvalidValue;
-  if (mf == 4) {
-    switch (a.nb) {
-      case 1: hipLaunchKernelGGL((conv3x3_kernel<1, 4>), grid, dim3(kNetThreads), lds, st, a); break;
-      case 2: hipLaunchKernelGGL((conv3x3_kernel<2, 4>), grid, dim3(kNetThreads), lds, st, a); break;
-      case 4: hipLaunchKernelGGL((conv3x3_kernel<4, 4>), grid, dim3(kNetThreads), lds, st, a); break;
-      default: return hipErrorInvalidValue;
-    }
-  } else {
-    switch (a.nb) {
-      case 1: hipLaunchKernelGGL((conv3x3_kernel<1, 2>), grid, dim3(kNetThreads), lds, st, a); break;
-      case 2: hipLaunchKernelGGL((conv3x3_kernel<2, 2>), grid, dim3(kNetThreads), lds, st, a); break;
-      case 4: hipLaunchKernelGGL((conv3x3_kernel<4, 2>), grid, dim3(kNetThreads), lds, st, a); break;
-      case 8: hipLaunchKernelGGL((conv3x3_kernel<8, 2>), grid, dim3(kNetThreads), lds, st, a); break;
-      default: return hipErrorInvalidValue;
-    }
+template <int NB>
+static hipError_t launch_conv_nb(const ConvArgs& a, int mf, dim3 grid, size_t lds, hipStream_t st) {
+  switch (mf) {
+    case 1: hipLaunchKernelGGL((conv3x3_kernel<NB, 1>), grid, dim3(kNetThreads), lds, st, a); break;
+    case 2: hipLaunchKernelGGL((conv3x3_kernel<NB, 2>), grid, dim3(kNetThreads), lds, st, a); break;
+    default: hipLaunchKernelGGL((conv3x3_kernel<NB, NB == 8 ? 2 : 4>), grid, dim3(kNetThreads), lds, st, a); break;
   }
   return hipGetLastError();
+}
+
+hipError_t launch_conv(const ConvArgs& a, int batch, hipStream_t st) {
+  const int npix = a.H * a.W;
+  const int mf = conv_mf(a.H, a.W, a.cinp, a.nb, batch);
+  const dim3 grid((npix + 64 * mf - 1) / (64 * mf), batch);
+  const size_t lds = conv_lds_bytes(a.H, a.W, a.cinp, mf);
+  // the largest layer taken: 160 KB of weight fragments and two-fragment band (128 channels into 64 are refused)
+  const size_t weights = (size_t)a.ksteps * a.nb * kWave * sizeof(bf16x8);
+  if (conv_lds_bytes(a.H, a.W, a.cinp, 2) + weights > 160 * 1024) return hipErrorInvalidValue;
+  if (lds > 160 * 1024 || (1 << a.lc) != a.cinp || a.ksteps % kConvSteps || (a.mode == kUpCat && 2 * a.c1 != a.cinp))
+    return hipErrorInvalidValue;
+  switch (a.nb) {
+    case 1: return launch_conv_nb<1>(a, mf, grid, lds, st);
+    case 2: return launch_conv_nb<2>(a, mf, grid, lds, st);
+    case 4: return launch_conv_nb<4>(a, mf, grid, lds, st);
+    case 8: return launch_conv_nb<8>(a, mf, grid, lds, st);
+    default: return hipErrorInvalidValue;
+  }
 }
 
 // ---- weight gradient ----------------------------------------------------------------
@@ -596,7 +741,7 @@ __device__ __forceinline__ cplx<float> tile_apply(const cplx<float>* tab, const 
 
 }  // namespace
 
-// One workgroup per tile.  Inference: y = a7 W8 + b8.  Training additionally forms, with
+// One workgroup per tile, training (inference: conv3x3_kernel).  Forms y = a7 W8 + b8 and, with
 // e = m (y - t) and r = B e (B the tile's subdomain operator, m its node mask),
 //   loss_b = w_res ||r||^2 / ||B t||^2 + w_err ||e||^2 / ||m t||^2,
 //   dL/dy  = (w_res 2 B^H r / ||B t||^2 + w_err 2 e / ||m t||^2) / batch   on nodes,
@@ -610,17 +755,14 @@ __global__ void __launch_bounds__(kNetThreads) head_kernel(HeadArgs a) {
   const int b = blockIdx.x, tid = threadIdx.x, T = a.T, npix = T * T;
   for (int i = tid; i < 2 * C + 2; i += kNetThreads)
     hw[i] = i < 2 * C ? a.params[a.woff + i] : a.params[a.boff + i - 2 * C];
-  TileDescDev d{0, 0, 0, 0, 0.0};
-  if (a.t) {
-    d = a.desc[b];
-    build_class_table<float>(d.robin, d.kh, d.kh * d.kh, tab);
-  }
+  const TileDescDev d = a.desc[b];
+  build_class_table<float>(d.robin, d.kh, d.kh * d.kh, tab);
   __syncthreads();
   const bf16* act = a.a7 + (size_t)b * npix * C;
   float* y = a.y + (size_t)b * npix * 2;
-  const float* t = a.t ? a.t + (size_t)b * npix * 2 : nullptr;
-  float* E = a.E ? a.E + (size_t)b * npix * 2 : nullptr;
-  float* R = a.R ? a.R + (size_t)b * npix * 2 : nullptr;
+  const float* t = a.t + (size_t)b * npix * 2;
+  float* E = a.E + (size_t)b * npix * 2;
+  float* R = a.R + (size_t)b * npix * 2;
   double num_err = 0.0, den_err = 0.0;
   for (int p = tid; p < npix; p += kNetThreads) {
     float y0 = hw[2 * C], y1 = hw[2 * C + 1];
@@ -631,17 +773,14 @@ __global__ void __launch_bounds__(kNetThreads) head_kernel(HeadArgs a) {
     }
     y[2 * p] = y0;
     y[2 * p + 1] = y1;
-    if (t) {
-      const int li = p % T, lj = p / T;
-      const bool node = li < d.nx && lj < d.ny;
-      const float e0 = node ? y0 - t[2 * p] : 0.0f, e1 = node ? y1 - t[2 * p + 1] : 0.0f;
-      E[2 * p] = e0;
-      E[2 * p + 1] = e1;
-      num_err += (double)e0 * e0 + (double)e1 * e1;
-      if (node) den_err += (double)t[2 * p] * t[2 * p] + (double)t[2 * p + 1] * t[2 * p + 1];
-    }
+    const int li = p % T, lj = p / T;
+    const bool node = li < d.nx && lj < d.ny;
+    const float e0 = node ? y0 - t[2 * p] : 0.0f, e1 = node ? y1 - t[2 * p + 1] : 0.0f;
+    E[2 * p] = e0;
+    E[2 * p + 1] = e1;
+    num_err += (double)e0 * e0 + (double)e1 * e1;
+    if (node) den_err += (double)t[2 * p] * t[2 * p] + (double)t[2 * p + 1] * t[2 * p + 1];
   }
-  if (!t) return;
   __syncthreads();
   double num_res = 0.0, den_res = 0.0;
   auto getE = [&](int i, int j) { return cplx<float>{E[2 * (j * T + i)], E[2 * (j * T + i) + 1]}; };
@@ -838,27 +977,15 @@ hipError_t launch_packed_to_tiles(const SubDesc* subs, int nsub, int nrhs, long 
 }
 
 hipError_t configure_net() {
-  const int lim = 160 * 1024;
-  hipError_t e;
-  if ((e = hipFuncSetAttribute((const void*)conv3x3_kernel<1, 4>, hipFuncAttributeMaxDynamicSharedMemorySize, lim)))
-    return e;
-  if ((e = hipFuncSetAttribute((const void*)conv3x3_kernel<2, 4>, hipFuncAttributeMaxDynamicSharedMemorySize, lim)))
-    return e;
-  if ((e = hipFuncSetAttribute((const void*)conv3x3_kernel<4, 4>, hipFuncAttributeMaxDynamicSharedMemorySize, lim)))
-    return e;
-  if ((e = hipFuncSetAttribute((const void*)conv3x3_kernel<8, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, lim)))
-    return e;
-  if ((e = hipFuncSetAttribute((const void*)conv3x3_kernel<1, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, lim)))
-    return e;
-  if ((e = hipFuncSetAttribute((const void*)conv3x3_kernel<2, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, lim)))
-    return e;
-  if ((e = hipFuncSetAttribute((const void*)conv3x3_kernel<4, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, lim)))
-    return e;
-  if ((e = hipFuncSetAttribute((const void*)conv3x3_wgrad_kernel<1>, hipFuncAttributeMaxDynamicSharedMemorySize, lim)))
-    return e;
-  if ((e = hipFuncSetAttribute((const void*)conv3x3_wgrad_kernel<2>, hipFuncAttributeMaxDynamicSharedMemorySize, lim)))
-    return e;
-  return hipFuncSetAttribute((const void*)conv3x3_wgrad_kernel<4>, hipFuncAttributeMaxDynamicSharedMemorySize, lim);
+  const void* kernels[] = {
+      (const void*)conv3x3_kernel<1, 1>, (const void*)conv3x3_kernel<1, 2>, (const void*)conv3x3_kernel<1, 4>,
+      (const void*)conv3x3_kernel<2, 1>, (const void*)conv3x3_kernel<2, 2>, (const void*)conv3x3_kernel<2, 4>,
+      (const void*)conv3x3_kernel<4, 1>, (const void*)conv3x3_kernel<4, 2>, (const void*)conv3x3_kernel<4, 4>,
+      (const void*)conv3x3_kernel<8, 1>, (const void*)conv3x3_kernel<8, 2>,
+      (const void*)conv3x3_wgrad_kernel<1>, (const void*)conv3x3_wgrad_kernel<2>, (const void*)conv3x3_wgrad_kernel<4>};
+  for (const void* k : kernels)
+    if (hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024)) return e;
+  return hipSuccess;
 }
 
 }  // namespace ddh
