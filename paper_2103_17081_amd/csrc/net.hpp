@@ -87,26 +87,28 @@ struct RouteArgs {
   const float* coarse; int cstride;
   const bf16* act;
   bf16* dz;
-  int H, W, C;
-  long long total;       // B * H * W * C
+  int H, W, lw, lcg;     // lw = log2(W), 8 2^lcg channels; strides and offsets are multiples of 8
 };
 
+constexpr int kMaxTile = 128;
+constexpr int kHeadRows = 8;         // rows of a strip of the head's training kernels
+constexpr int head_strips(int T) { return T / kHeadRows; }
+
+// The head's training pass; strips of a tile follow each other.
 struct HeadArgs {
   const bf16* a7;
   const float* params;
   long long woff, boff;
-  int c1, T;
-  float* y;              // [B][T][T][2]
+  int c1, T, lt;         // lt = log2(T)
   const float* t;        // targets [B][T][T][2]
   const TileDescDev* desc;
   double w_res, w_err;
   int batch;
-  float* E;              // scratch [B][T][T][2]
-  float* R;              // scratch [B][T][T][2]
+  double* den;           // [B strips][2] denominators
   bf16* dz7;             // [B][T][T][c1]
-  float* part;           // [B][c1][2] weight partials
-  float* bpart;          // [B][2] bias partials
-  double* loss;          // [B]
+  float* part;           // [B strips][c1][2] weight partials
+  float* bpart;          // [B strips][2] bias partials
+  double* loss;          // [B strips]
 };
 
 struct TileArgs {
@@ -131,7 +133,7 @@ hipError_t launch_conv_wgrad(const ConvArgs& a, const bf16* dz, int cout, int ba
 int wgrad_partials(int H, int W, int cinp, int cout, int batch);
 hipError_t launch_wgrad_reduce(const float* part, const float* bpart, int groups, int cin, int cinp, int cout,
                                int taps, float* gW, float* gb, hipStream_t st);
-hipError_t launch_route(const RouteArgs& a, hipStream_t st);
+hipError_t launch_route(const RouteArgs& a, int batch, hipStream_t st);
 hipError_t launch_head(const HeadArgs& a, hipStream_t st);
 hipError_t launch_adam(float* p, const float* g, float* m, float* v, long long n, float lr, float b1, float b2,
                        float eps, float c1, float c2, hipStream_t st);

@@ -120,6 +120,10 @@ ddh::ConvArgs layer_args(const dd_net* n, int i) {
   return a;
 }
 
+void fill_normal(float* w, long long count, double sd, std::normal_distribution<double>& nd, std::mt19937_64& rng) {
+  for (long long q = 0; q < count; ++q) w[q] = (float)(sd * nd(rng));
+}
+
 dd_status prepare(dd_net* n, hipStream_t st) {
   NET_HIP(ddh::launch_net_prepare(n->nt, n->params, n->frags, st));
   return DD_OK;
@@ -128,7 +132,7 @@ dd_status prepare(dd_net* n, hipStream_t st) {
 dd_status backward(dd_net* n, int batch, hipStream_t st) {
   const ddh::NetTable& nt = n->nt;
   // head weights and bias
-  NET_HIP(ddh::launch_wgrad_reduce(n->part, n->bpart, batch, nt.c1, nt.c1, 2, 1, n->grads + nt.hwoff,
+  NET_HIP(ddh::launch_wgrad_reduce(n->part, n->bpart, batch * ddh::head_strips(n->T), nt.c1, nt.c1, 2, 1, n->grads + nt.hwoff,
                                    n->grads + nt.hboff, st));
   for (int i = ddh::kNetConv - 1; i >= 0; --i) {
     const ddh::NetLayer& L = nt.l[i];
@@ -159,8 +163,8 @@ dd_status backward(dd_net* n, int batch, hipStream_t st) {
     r.act = n->act[ti];
     r.dz = n->dz[ti];
     r.H = r.W = n->H(P.level);
-    r.C = P.cout;
-    r.total = (long long)batch * r.H * r.W * r.C;
+    r.lw = log2i(r.W);
+    r.lcg = log2i(P.cout) - 3;
     if (L.mode == ddh::kUpCat) {
       // input cat(up(a_ti), skip): the first P.cout channels come from a_ti
       r.fine = n->dc[i];
@@ -179,7 +183,7 @@ dd_status backward(dd_net* n, int batch, hipStream_t st) {
       r.coarse = n->dc[i];
       r.cstride = L.cin;
     }
-    NET_HIP(ddh::launch_route(r, st));
+    NET_HIP(ddh::launch_route(r, batch, st));
   }
   return DD_OK;
 }
@@ -277,7 +281,8 @@ dd_status dd_net_create(const dd_net_params* p, dd_net** out) {
     NET_A(n->grads, (size_t)n->nparams);
     NET_A(n->m, (size_t)n->nparams);
     NET_A(n->v, (size_t)n->nparams);
-    size_t part = B * 2 * (size_t)n->nt.c1, bpart = B * 2;   // the head's, one per tile
+    const size_t strips = B * ddh::head_strips(n->T);
+    size_t part = strips * 2 * (size_t)n->nt.c1, bpart = strips * 2;   // the head's
     for (int i = 0; i < ddh::kNetConv; ++i) {
       const ddh::NetLayer& L = n->nt.l[i];
       const int H = n->H(L.level);
@@ -287,12 +292,11 @@ dd_status dd_net_create(const dd_net_params* p, dd_net** out) {
       part = std::max(part, groups * 9 * L.cinp * L.cout);
       bpart = std::max(bpart, groups * L.cout);
     }
-    NET_A(n->E, B * T2 * 2);
-    NET_A(n->R, B * T2 * 2);
     NET_A(n->t, B * T2 * 2);
     NET_A(n->part, part);
     NET_A(n->bpart, bpart);
-    NET_A(n->loss, B);
+    NET_A(n->loss, strips);
+    NET_A(n->den, strips * 2);
     NET_A(n->desc, B);
   }
 #undef NET_A
@@ -308,9 +312,9 @@ dd_status dd_net_create(const dd_net_params* p, dd_net** out) {
   for (int i = 0; i < ddh::kNetConv; ++i) {
     const ddh::NetLayer& L = n->nt.l[i];
     const double sd = std::sqrt(2.0 / (9.0 * L.cin));
-    for (long long q = 0; q < 9LL * L.cin * L.cout; ++q) w[L.woff + q] = (float)(sd * nd(rng));
+    fill_normal(w.data() + L.woff, 9LL * L.cin * L.cout, sd, nd, rng);
   }
-  for (long long q = 0; q < 2LL * n->nt.c1; ++q) w[n->nt.hwoff + q] = (float)(std::sqrt(2.0 / n->nt.c1) * nd(rng));
+  fill_normal(w.data() + n->nt.hwoff, 2LL * n->nt.c1, std::sqrt(2.0 / n->nt.c1), nd, rng);
   *out = n;
   s = dd_net_set_params(n, w.data(), n->nparams);
   if (s != DD_OK) {
@@ -472,14 +476,13 @@ dd_status dd_net_gradient(dd_net* n, const float* x, const float* t, const dd_ti
   h.boff = n->nt.hboff;
   h.c1 = n->nt.c1;
   h.T = n->T;
-  h.y = n->y;
+  h.lt = log2i(n->T);
   h.t = t;
   h.desc = n->desc;
   h.w_res = w_res;
   h.w_err = w_err;
   h.batch = batch;
-  h.E = n->E;
-  h.R = n->R;
+  h.den = n->den;
   h.dz7 = n->dz[ddh::kNetConv - 1];
   h.part = n->part;
   h.bpart = n->bpart;
@@ -487,8 +490,8 @@ dd_status dd_net_gradient(dd_net* n, const float* x, const float* t, const dd_ti
   NET_HIP(ddh::launch_head(h, st));
   NET_TRY(backward(n, batch, st));
   if (grad) NET_HIP(hipMemcpyAsync(grad, n->grads, (size_t)n->nparams * sizeof(float), hipMemcpyDeviceToDevice, st));
-  std::vector<double> lp(batch);
-  NET_HIP(hipMemcpyAsync(lp.data(), n->loss, (size_t)batch * sizeof(double), hipMemcpyDeviceToHost, st));
+  std::vector<double> lp((size_t)batch * ddh::head_strips(n->T));
+  NET_HIP(hipMemcpyAsync(lp.data(), n->loss, lp.size() * sizeof(double), hipMemcpyDeviceToHost, st));
   NET_HIP(hipStreamSynchronize(st));
   if (loss) {
     double s = 0.0;

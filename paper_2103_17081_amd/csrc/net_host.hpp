@@ -25,12 +25,11 @@ struct dd_net {
   float* v = nullptr;
   ddh::bf16* dz[ddh::kNetConv] = {};
   float* dc[ddh::kNetConv] = {};     // data gradient at the input of layer i (i >= 1)
-  float* E = nullptr;
-  float* R = nullptr;
   float* t = nullptr;
   float* part = nullptr;
   float* bpart = nullptr;
-  double* loss = nullptr;
+  double* loss = nullptr;            // one per strip of a tile
+  double* den = nullptr;
   ddh::TileDescDev* desc = nullptr;
   long long adam_t = 0;
   std::vector<void*> allocs;

@@ -672,33 +672,43 @@ hipError_t launch_net_prepare(const NetTable& nt, const float* params, bf16x8* f
 
 // ---- gradient routing between levels ----------------------------------------------------
 
-__global__ void route_kernel(RouteArgs a) {
-  for (long long idx = blockIdx.x * (long long)blockDim.x + threadIdx.x; idx < a.total;
-       idx += (long long)gridDim.x * blockDim.x) {
-    const int c = (int)(idx % a.C);
-    const long long pix = idx / a.C;
-    const int x = (int)(pix % a.W);
-    const long long r = pix / a.W;
-    const int y = (int)(r % a.H);
-    const long long b = r / a.H;
-    float g = 0.0f;
-    if (a.fine) {
-      const int Wf = 2 * a.W;
-      const float* f = a.fine + (((b * 2 * a.H) + 2 * y) * Wf + 2 * x) * a.fstride + a.foff + c;
-      g += (f[0] + f[a.fstride]) + (f[(long long)Wf * a.fstride] + f[(long long)Wf * a.fstride + a.fstride]);
-    }
-    if (a.same) g += a.same[pix * a.sstride + a.soff + c];
-    if (a.coarse) {
-      const int Wc = a.W >> 1;
-      g += 0.25f * a.coarse[((b * (a.H >> 1) + (y >> 1)) * Wc + (x >> 1)) * a.cstride + c];
-    }
-    a.dz[idx] = (float)a.act[idx] > 0.0f ? (bf16)g : (bf16)0.0f;
+// Grid: (units of 8 channels of a tile / 256, batch). Bound by latency and its reads, up to 6 fp32 values per
+// output: one element per thread, with 64-bit divisions for its place, took 17 us at the largest level of 64
+// tiles of 64 x 64, now 10.
+__global__ void __launch_bounds__(kNetThreads) route_kernel(RouteArgs a) {
+  const int u = blockIdx.x * kNetThreads + threadIdx.x, npix = a.H * a.W;
+  if (u >= npix << a.lcg) return;
+  const int c = (u & ((1 << a.lcg) - 1)) * 8, p = u >> a.lcg, x = p & (a.W - 1), y = p >> a.lw;
+  const size_t b = blockIdx.y, pix = b * npix + p;
+  const bf16x8 act = *(const bf16x8*)(a.act + (pix << (a.lcg + 3)) + c);
+  f32x4 g[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+  if (a.fine) {
+    const float* f = a.fine + (4 * b * npix + 4 * y * a.W + 2 * x) * a.fstride + a.foff + c;
+    const float* d = f + (size_t)2 * a.W * a.fstride;
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+      g[h] += (*(const f32x4*)(f + 4 * h) + *(const f32x4*)(f + a.fstride + 4 * h)) +
+              (*(const f32x4*)(d + 4 * h) + *(const f32x4*)(d + a.fstride + 4 * h));
   }
+  if (a.same) {
+    const float* f = a.same + pix * a.sstride + a.soff + c;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) g[h] += *(const f32x4*)(f + 4 * h);
+  }
+  if (a.coarse) {
+    const float* f = a.coarse + (b * (npix >> 2) + (y >> 1) * (a.W >> 1) + (x >> 1)) * a.cstride + c;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) g[h] += 0.25f * *(const f32x4*)(f + 4 * h);
+  }
+  bf16x8 o;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) o[i] = (float)act[i] > 0.0f ? (bf16)g[i / 4][i % 4] : (bf16)0.0f;
+  *(bf16x8*)(a.dz + (pix << (a.lcg + 3)) + c) = o;
 }
 
-hipError_t launch_route(const RouteArgs& a, hipStream_t st) {
-  const int blocks = (int)std::min<long long>((a.total + 255) / 256, 8192);
-  hipLaunchKernelGGL(route_kernel, dim3(blocks), dim3(256), 0, st, a);
+hipError_t launch_route(const RouteArgs& a, int batch, hipStream_t st) {
+  const int units = a.H * a.W << a.lcg;
+  hipLaunchKernelGGL(route_kernel, dim3((units + kNetThreads - 1) / kNetThreads, batch), dim3(kNetThreads), 0, st, a);
   return hipGetLastError();
 }
 
@@ -718,141 +728,186 @@ __device__ __forceinline__ double block_sum_d(double v, double* red) {
   return s;
 }
 
-// (B v)_p for node p = (li, lj) of the tile operator, v read through `get` (complex).
-template <typename Get>
+// (B v)_p for node p = (li, lj) of the tile operator; v at p's place in LDS rows of stride T + 2, zero
+// where there is no node.
 __device__ __forceinline__ cplx<float> tile_apply(const cplx<float>* tab, const TileDescDev& d, int li, int lj,
-                                                  Get get) {
+                                                  const cplx<float>* v, int stride) {
   const int xc = (li == 0 && (d.edges & 1)) ? 0 : ((li == d.nx - 1 && (d.edges & 2)) ? 2 : 1);
   const int yc = (lj == 0 && (d.edges & 4)) ? 0 : ((lj == d.ny - 1 && (d.edges & 8)) ? 2 : 1);
   const cplx<float>* c = tab + kStencilPts * (3 * yc + xc);
-  cplx<float> acc = c[kC] * get(li, lj);
-  if (li > 0) acc = cfma(c[kW], get(li - 1, lj), acc);
-  if (li < d.nx - 1) acc = cfma(c[kE], get(li + 1, lj), acc);
-  if (lj > 0) {
-    acc = cfma(c[kS], get(li, lj - 1), acc);
-    if (li > 0) acc = cfma(c[kSW], get(li - 1, lj - 1), acc);
-  }
-  if (lj < d.ny - 1) {
-    acc = cfma(c[kN], get(li, lj + 1), acc);
-    if (li < d.nx - 1) acc = cfma(c[kNE], get(li + 1, lj + 1), acc);
-  }
-  return acc;
+  cplx<float> acc = c[kC] * v[0];
+  acc = cfma(c[kW], v[-1], acc);
+  acc = cfma(c[kE], v[1], acc);
+  acc = cfma(c[kS], v[-stride], acc);
+  acc = cfma(c[kSW], v[-stride - 1], acc);
+  acc = cfma(c[kN], v[stride], acc);
+  return cfma(c[kNE], v[stride + 1], acc);
+}
+
+__device__ __forceinline__ void zero_sides(cplx<float>* f, int rows, int T) {
+  for (int u = threadIdx.x; u < 2 * rows; u += kNetThreads) f[(u >> 1) * (T + 2) + (u & 1) * (T + 1)] = czero<float>();
 }
 
 }  // namespace
 
-// One workgroup per tile, training (inference: conv3x3_kernel).  Forms y = a7 W8 + b8 and, with
-// e = m (y - t) and r = B e (B the tile's subdomain operator, m its node mask),
+// The loss of tile b, with e = m (y - t) and r = B e (y = a7 W8 + b8, B the tile's subdomain operator, m its
+// node mask), and its gradient:
 //   loss_b = w_res ||r||^2 / ||B t||^2 + w_err ||e||^2 / ||m t||^2,
 //   dL/dy  = (w_res 2 B^H r / ||B t||^2 + w_err 2 e / ||m t||^2) / batch   on nodes,
 // then the head's weight and bias partials and dz7 = (dL/dy W8^T) * (a7 > 0).
+//
+// The denominators depend on the target alone, so a first launch sums them and the second one needs
+// no other sum over a tile: both take strips of kHeadRows rows, and the second forms e on two and r on one more
+// row to each side itself. One workgroup per tile, with e and r in global memory, was a chain of
+// three passes on a quarter of the chip: 125 us for 64 tiles of 64 x 64, both launches now 18.
+//
+// den[b][strip] = (||m t||^2, ||B t||^2) over the strip.  Grid: (T / kHeadRows, batch).
+__global__ void __launch_bounds__(kNetThreads) head_norms_kernel(HeadArgs a) {
+  __shared__ cplx<float> tab[kClasses * kStencilPts];
+  __shared__ double red[kNetThreads / kWave];
+  __shared__ cplx<float> f[(kHeadRows + 2) * (kMaxTile + 2)];
+  const int b = blockIdx.y, T = a.T, lt = a.lt, S = T + 2, y0 = blockIdx.x * kHeadRows;
+  const TileDescDev d = a.desc[b];
+  build_class_table<float>(d.robin, d.kh, d.kh * d.kh, tab);
+  zero_sides(f, kHeadRows + 2, T);
+  const float* t = a.t + ((size_t)b << (2 * lt + 1));
+  double err = 0.0, res = 0.0;
+  for (int u = threadIdx.x; u < (kHeadRows + 2) << lt; u += kNetThreads) {
+    const int r = u >> lt, li = u & (T - 1), lj = y0 - 1 + r;
+    cplx<float> v = czero<float>();
+    if (li < d.nx && lj >= 0 && lj < d.ny) v = cplx<float>{t[2 * (lj * T + li)], t[2 * (lj * T + li) + 1]};
+    f[r * S + li + 1] = v;
+    if (r >= 1 && r <= kHeadRows) err += (double)v.re * v.re + (double)v.im * v.im;
+  }
+  __syncthreads();
+  for (int u = threadIdx.x; u < kHeadRows << lt; u += kNetThreads) {
+    const int r = u >> lt, li = u & (T - 1), lj = y0 + r;
+    if (li < d.nx && lj < d.ny) res += (double)cabs2(tile_apply(tab, d, li, lj, f + (r + 1) * S + li + 1, S));
+  }
+  err = block_sum_d(err, red);
+  res = block_sum_d(res, red);
+  if (threadIdx.x == 0) {
+    double* o = a.den + 2 * ((size_t)b * gridDim.x + blockIdx.x);
+    o[0] = err;
+    o[1] = res;
+  }
+}
+
+// loss, part and bpart: one value or row per strip.  Grid: (T / kHeadRows, batch).
 template <int C>
 __global__ void __launch_bounds__(kNetThreads) head_kernel(HeadArgs a) {
   __shared__ cplx<float> tab[kClasses * kStencilPts];
   __shared__ double red[kNetThreads / kWave];
   __shared__ float hw[C * 2 + 2];
   __shared__ float pred[kNetThreads / kWave][C * 2 + 2];
-  const int b = blockIdx.x, tid = threadIdx.x, T = a.T, npix = T * T;
+  __shared__ cplx<float> E[(kHeadRows + 4) * (kMaxTile + 2)];
+  __shared__ cplx<float> R[(kHeadRows + 2) * (kMaxTile + 2)];
+  const int b = blockIdx.y, tid = threadIdx.x, T = a.T, lt = a.lt, S = T + 2, y0 = blockIdx.x * kHeadRows;
+  const size_t strip = (size_t)b * gridDim.x + blockIdx.x;
   for (int i = tid; i < 2 * C + 2; i += kNetThreads)
     hw[i] = i < 2 * C ? a.params[a.woff + i] : a.params[a.boff + i - 2 * C];
   const TileDescDev d = a.desc[b];
   build_class_table<float>(d.robin, d.kh, d.kh * d.kh, tab);
-  __syncthreads();
-  const bf16* act = a.a7 + (size_t)b * npix * C;
-  float* y = a.y + (size_t)b * npix * 2;
-  const float* t = a.t + (size_t)b * npix * 2;
-  float* E = a.E + (size_t)b * npix * 2;
-  float* R = a.R + (size_t)b * npix * 2;
-  double num_err = 0.0, den_err = 0.0;
-  for (int p = tid; p < npix; p += kNetThreads) {
-    float y0 = hw[2 * C], y1 = hw[2 * C + 1];
-    for (int c = 0; c < C; ++c) {
-      const float v = (float)act[(size_t)p * C + c];
-      y0 = fmaf(v, hw[2 * c], y0);
-      y1 = fmaf(v, hw[2 * c + 1], y1);
-    }
-    y[2 * p] = y0;
-    y[2 * p + 1] = y1;
-    const int li = p % T, lj = p / T;
-    const bool node = li < d.nx && lj < d.ny;
-    const float e0 = node ? y0 - t[2 * p] : 0.0f, e1 = node ? y1 - t[2 * p + 1] : 0.0f;
-    E[2 * p] = e0;
-    E[2 * p + 1] = e1;
-    num_err += (double)e0 * e0 + (double)e1 * e1;
-    if (node) den_err += (double)t[2 * p] * t[2 * p] + (double)t[2 * p + 1] * t[2 * p + 1];
+  zero_sides(E, kHeadRows + 4, T);
+  zero_sides(R, kHeadRows + 2, T);
+  double den_err = 0.0, den_res = 0.0;
+  for (unsigned s = 0; s < gridDim.x; ++s) {
+    den_err += a.den[2 * ((size_t)b * gridDim.x + s)];
+    den_res += a.den[2 * ((size_t)b * gridDim.x + s) + 1];
   }
-  __syncthreads();
-  double num_res = 0.0, den_res = 0.0;
-  auto getE = [&](int i, int j) { return cplx<float>{E[2 * (j * T + i)], E[2 * (j * T + i) + 1]}; };
-  auto getT = [&](int i, int j) { return cplx<float>{t[2 * (j * T + i)], t[2 * (j * T + i) + 1]}; };
-  for (int p = tid; p < npix; p += kNetThreads) {
-    const int li = p % T, lj = p / T;
-    cplx<float> r = czero<float>();
-    if (li < d.nx && lj < d.ny) {
-      r = tile_apply(tab, d, li, lj, getE);
-      const cplx<float> bt = tile_apply(tab, d, li, lj, getT);
-      num_res += (double)cabs2(r);
-      den_res += (double)cabs2(bt);
-    }
-    R[2 * p] = r.re;
-    R[2 * p + 1] = r.im;
-  }
-  num_err = block_sum_d(num_err, red);
-  den_err = block_sum_d(den_err, red);
-  num_res = block_sum_d(num_res, red);
-  den_res = block_sum_d(den_res, red);
   if (den_err <= 0.0) den_err = 1.0;
   if (den_res <= 0.0) den_res = 1.0;
-  if (tid == 0) a.loss[b] = a.w_res * num_res / den_res + a.w_err * num_err / den_err;
+  __syncthreads();
+  const bf16* act = a.a7 + ((size_t)b << (2 * lt)) * C;
+  const float* t = a.t + ((size_t)b << (2 * lt + 1));
+  double num_err = 0.0, num_res = 0.0;
+  for (int u = tid; u < (kHeadRows + 4) << lt; u += kNetThreads) {
+    const int r = u >> lt, li = u & (T - 1), lj = y0 - 2 + r, p = lj * T + li;
+    cplx<float> e = czero<float>();
+    if (li < d.nx && lj >= 0 && lj < d.ny) {
+      float v0 = hw[2 * C], v1 = hw[2 * C + 1];
+#pragma unroll
+      for (int c8 = 0; c8 < C / 8; ++c8) {
+        const bf16x8 av = *(const bf16x8*)(act + (size_t)p * C + 8 * c8);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          v0 = fmaf((float)av[i], hw[2 * (8 * c8 + i)], v0);
+          v1 = fmaf((float)av[i], hw[2 * (8 * c8 + i) + 1], v1);
+        }
+      }
+      e = cplx<float>{v0 - t[2 * p], v1 - t[2 * p + 1]};
+    }
+    E[r * S + li + 1] = e;
+    if (r >= 2 && r < kHeadRows + 2) num_err += (double)e.re * e.re + (double)e.im * e.im;
+  }
+  __syncthreads();
+  // R holds conj(r): B^H r = conj(B conj(r)) (B is complex symmetric)
+  for (int u = tid; u < (kHeadRows + 2) << lt; u += kNetThreads) {
+    const int r = u >> lt, li = u & (T - 1), lj = y0 - 1 + r;
+    cplx<float> v = czero<float>();
+    if (li < d.nx && lj >= 0 && lj < d.ny) v = tile_apply(tab, d, li, lj, E + (r + 1) * S + li + 1, S);
+    R[r * S + li + 1] = cplx<float>{v.re, -v.im};
+    if (r >= 1 && r <= kHeadRows) num_res += (double)cabs2(v);
+  }
+  __syncthreads();
   const float sres = (float)(2.0 * a.w_res / (den_res * a.batch));
   const float serr = (float)(2.0 * a.w_err / (den_err * a.batch));
-  // B^H r = conj(B conj(r)) (B is complex symmetric)
-  auto getRc = [&](int i, int j) { return cplx<float>{R[2 * (j * T + i)], -R[2 * (j * T + i) + 1]}; };
   float pw[C * 2 + 2];
 #pragma unroll
   for (int i = 0; i < 2 * C + 2; ++i) pw[i] = 0.0f;
-  bf16* dz = a.dz7 + (size_t)b * npix * C;
-  for (int p = tid; p < npix; p += kNetThreads) {
-    const int li = p % T, lj = p / T;
+  bf16* dz = a.dz7 + ((size_t)b << (2 * lt)) * C;
+  for (int u = tid; u < kHeadRows << lt; u += kNetThreads) {
+    const int r = u >> lt, li = u & (T - 1), lj = y0 + r, p = lj * T + li;
     float g0 = 0.0f, g1 = 0.0f;
     if (li < d.nx && lj < d.ny) {
-      const cplx<float> q = tile_apply(tab, d, li, lj, getRc);
-      g0 = sres * q.re + serr * E[2 * p];
-      g1 = -sres * q.im + serr * E[2 * p + 1];
+      const cplx<float> q = tile_apply(tab, d, li, lj, R + (r + 1) * S + li + 1, S);
+      const cplx<float> e = E[(r + 2) * S + li + 1];
+      g0 = sres * q.re + serr * e.re;
+      g1 = -sres * q.im + serr * e.im;
     }
     pw[2 * C] += g0;
     pw[2 * C + 1] += g1;
 #pragma unroll
-    for (int c = 0; c < C; ++c) {
-      const float v = (float)act[(size_t)p * C + c];
-      pw[2 * c] = fmaf(v, g0, pw[2 * c]);
-      pw[2 * c + 1] = fmaf(v, g1, pw[2 * c + 1]);
-      const float da = g0 * hw[2 * c] + g1 * hw[2 * c + 1];
-      dz[(size_t)p * C + c] = v > 0.0f ? (bf16)da : (bf16)0.0f;
+    for (int c8 = 0; c8 < C / 8; ++c8) {
+      const bf16x8 av = *(const bf16x8*)(act + (size_t)p * C + 8 * c8);
+      bf16x8 o;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const int c = 8 * c8 + i;
+        const float v = (float)av[i];
+        pw[2 * c] = fmaf(v, g0, pw[2 * c]);
+        pw[2 * c + 1] = fmaf(v, g1, pw[2 * c + 1]);
+        o[i] = v > 0.0f ? (bf16)(g0 * hw[2 * c] + g1 * hw[2 * c + 1]) : (bf16)0.0f;
+      }
+      *(bf16x8*)(dz + (size_t)p * C + 8 * c8) = o;
     }
   }
+  num_err = block_sum_d(num_err, red);
+  num_res = block_sum_d(num_res, red);
+  if (tid == 0) a.loss[strip] = a.w_res * num_res / den_res + a.w_err * num_err / den_err;
   const int lane = tid & 63, wave = tid >> 6;
 #pragma unroll
   for (int i = 0; i < 2 * C + 2; ++i) {
-    const float s = wave_sum(pw[i]);
-    if (lane == 0) pred[wave][i] = s;
+    const float s = wave_total(pw[i]);
+    if (lane == kWave - 1) pred[wave][i] = s;
   }
   __syncthreads();
   for (int i = tid; i < 2 * C + 2; i += kNetThreads) {
     float s = 0.0f;
 #pragma unroll
     for (int w = 0; w < kNetThreads / kWave; ++w) s += pred[w][i];
-    if (i < 2 * C) a.part[(size_t)b * 2 * C + i] = s;
-    else a.bpart[(size_t)b * 2 + i - 2 * C] = s;
+    if (i < 2 * C) a.part[strip * 2 * C + i] = s;
+    else a.bpart[strip * 2 + i - 2 * C] = s;
   }
 }
 
 hipError_t launch_head(const HeadArgs& a, hipStream_t st) {
+  const dim3 grid(head_strips(a.T), a.batch);
+  hipLaunchKernelGGL(head_norms_kernel, grid, dim3(kNetThreads), 0, st, a);
   switch (a.c1) {
-    case 16: hipLaunchKernelGGL(head_kernel<16>, dim3(a.batch), dim3(kNetThreads), 0, st, a); break;
-    case 32: hipLaunchKernelGGL(head_kernel<32>, dim3(a.batch), dim3(kNetThreads), 0, st, a); break;
-    case 48: hipLaunchKernelGGL(head_kernel<48>, dim3(a.batch), dim3(kNetThreads), 0, st, a); break;
-    case 64: hipLaunchKernelGGL(head_kernel<64>, dim3(a.batch), dim3(kNetThreads), 0, st, a); break;
+    case 16: hipLaunchKernelGGL(head_kernel<16>, grid, dim3(kNetThreads), 0, st, a); break;
+    case 32: hipLaunchKernelGGL(head_kernel<32>, grid, dim3(kNetThreads), 0, st, a); break;
+    case 64: hipLaunchKernelGGL(head_kernel<64>, grid, dim3(kNetThreads), 0, st, a); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
