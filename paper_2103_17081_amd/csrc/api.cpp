@@ -115,7 +115,7 @@ struct dd_handle {
   double* res_h = nullptr;      // pinned
   hipEvent_t ev[8] = {};        // phase timers of dd_solve
   bool ev_ok = false;
-  int* jdev = nullptr;          // device-side outer step index
+  int* jdev = nullptr;          // device-side outer step index, and the workgroups that have read it
   // launch configuration (dd_autotune)
   int inner_nt = ddh::kInnerThreads;
   bool lpt = true;              // subdomain solves launched largest tile first
@@ -599,7 +599,7 @@ dd_status dd_setup(const dd_params* p, void* stream, dd_handle** out) {
     DD_TRY(h->alloc(&o.done, h->nrhs));
     DD_TRY(h->alloc(&o.applies, h->nrhs));
     DD_TRY(h->alloc(&o.sweep_bytes, 2));
-    DD_TRY(h->alloc(&h->jdev, 1));
+    DD_TRY(h->alloc(&h->jdev, 2));
     const int slots = std::max(1, h->p.graph_steps);
     h->sev.resize((size_t)slots * kEvPerStep);
     for (auto& e : h->sev) DD_HIP(hipEventCreate(&e));
@@ -744,13 +744,11 @@ static dd_status enqueue_outer_step(dd_handle* h, int slot, hipStream_t st, bool
   DD_HIP(ddh::launch_dots2(h->Vo, vstr, nullptr, 0, nullptr, 0, nd, sr, 1, m, h->part, h->pstride, nr, o.done, st,
                            h->dots_blocks));
   DD_TRY(mark(5));
-  DD_HIP(ddh::launch_reduce_chunks(h->part, nd, h->pstride, sr, 2, 3, m, h->coef, h->pstride, nr, o.done, st));
-  DD_HIP(ddh::launch_dcgs2_step(o, sr, m, nd, h->coef, h->pstride, 1, h->ca, h->cb, m, h->scal, nr, st));
+  DD_HIP(ddh::launch_dcgs2_step(o, sr, m, nd, h->part, h->pstride, h->coef, 1, h->ca, h->cb, m, h->scal, h->jdev, nr,
+                                st));
   DD_TRY(mark(6));
-  DD_HIP(ddh::launch_dcgs2_update(h->Vo, vstr, nd, sr, h->ca, h->cb, m, h->scal, nr, o.done, st));
-  DD_TRY(mark(7));
-  DD_HIP(ddh::launch_advance_step(h->jdev, st));
-  return DD_OK;
+  DD_HIP(ddh::launch_dcgs2_update(h->Vo, vstr, nd, ddh::device_step(h->jdev, -1), h->ca, h->cb, m, h->scal, nr, o.done, st));
+  return mark(7);
 }
 
 // Capture graph_steps consecutive outer steps once per handle (on a private stream:
@@ -815,7 +813,7 @@ dd_status dd_solve(dd_handle* h, const void* fv, void* uv, void* stream, dd_stat
                                     h->pstride, nullptr, 0, 2, nr, nullptr, st));
     DD_HIP(ddh::launch_cycle_init(o, nr, st));
     DD_HIP(ddh::launch_scale(h->Vo, vstr, h->Vo, vstr, nd, o.hnext, kOuterBlocks, nr, o.done, st));
-    DD_HIP(hipMemsetAsync(h->jdev, 0, sizeof(int), st));
+    DD_HIP(hipMemsetAsync(h->jdev, 0, 2 * sizeof(int), st));
     o.first_cycle = 0;
     DD_TRY(sync_done());
     if (all_done) break;
@@ -853,10 +851,8 @@ dd_status dd_solve(dd_handle* h, const void* fv, void* uv, void* stream, dd_stat
       // end of a cycle: finalise column m-1 from v~_m alone
       DD_HIP(ddh::launch_dots2(h->Vo, vstr, h->Vo + (long long)m * nd, vstr, nullptr, 0, nd, ddh::host_step(m), 0, m,
                                h->part, h->pstride, nr, o.done, st, h->dots_blocks));
-      DD_HIP(ddh::launch_reduce_chunks(h->part, nd, h->pstride, ddh::host_step(m), 2, 3, m, h->coef, h->pstride, nr,
-                                       o.done, st));
-      DD_HIP(ddh::launch_dcgs2_step(o, ddh::host_step(m), m, nd, h->coef, h->pstride, 0, h->ca, h->cb, m, h->scal,
-                                    nr, st));
+      DD_HIP(ddh::launch_dcgs2_step(o, ddh::host_step(m), m, nd, h->part, h->pstride, h->coef, 0, h->ca, h->cb, m,
+                                    h->scal, nullptr, nr, st));
       DD_TRY(sync_done());
     }
     // u += Z y over the columns each right-hand side finalised in this cycle
