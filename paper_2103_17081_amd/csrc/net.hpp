@@ -111,6 +111,20 @@ struct HeadArgs {
   double* loss;          // [B strips]
 };
 
+// Sum of one layer's gradient partials.
+struct ReduceLayer {
+  const float* part;     // [groups][taps cinp][cout]
+  const float* bpart;    // [groups][cout]
+  float* gW;
+  float* gb;
+  int groups, cin, cinp, cout, taps;
+  int block;             // first workgroup
+};
+
+struct ReduceArgs {
+  ReduceLayer l[kNetConv + 1];   // the head last
+};
+
 struct TileArgs {
   const SubDesc* subs;
   Consts cs;
@@ -131,8 +145,8 @@ hipError_t launch_conv_wgrad(const ConvArgs& a, const bf16* dz, int cout, int ba
                              hipStream_t st);
 // Partials that launch_conv_wgrad writes (rows of part and bpart); grows with the batch.
 int wgrad_partials(int H, int W, int cinp, int cout, int batch);
-hipError_t launch_wgrad_reduce(const float* part, const float* bpart, int groups, int cin, int cinp, int cout,
-                               int taps, float* gW, float* gb, hipStream_t st);
+// Sums the partials of all layers (`block` is set by the launch).
+hipError_t launch_wgrad_reduce(ReduceArgs a, hipStream_t st);
 hipError_t launch_route(const RouteArgs& a, int batch, hipStream_t st);
 hipError_t launch_head(const HeadArgs& a, hipStream_t st);
 hipError_t launch_adam(float* p, const float* g, float* m, float* v, long long n, float lr, float b1, float b2,

@@ -120,6 +120,13 @@ ddh::ConvArgs layer_args(const dd_net* n, int i) {
   return a;
 }
 
+// Floats of a partial weight and bias gradient of layer i (the head after the 3x3 layers); both are multiples of
+// 4 except the head's biases, which come last.
+size_t part_floats(const dd_net* n, int i) {
+  return i < ddh::kNetConv ? (size_t)9 * n->nt.l[i].cinp * n->nt.l[i].cout : (size_t)2 * n->nt.c1;
+}
+size_t bias_floats(const dd_net* n, int i) { return i < ddh::kNetConv ? (size_t)n->nt.l[i].cout : 2; }
+
 void fill_normal(float* w, long long count, double sd, std::normal_distribution<double>& nd, std::mt19937_64& rng) {
   for (long long q = 0; q < count; ++q) w[q] = (float)(sd * nd(rng));
 }
@@ -131,16 +138,15 @@ dd_status prepare(dd_net* n, hipStream_t st) {
 
 dd_status backward(dd_net* n, int batch, hipStream_t st) {
   const ddh::NetTable& nt = n->nt;
-  // head weights and bias
-  NET_HIP(ddh::launch_wgrad_reduce(n->part, n->bpart, batch * ddh::head_strips(n->T), nt.c1, nt.c1, 2, 1, n->grads + nt.hwoff,
-                                   n->grads + nt.hboff, st));
+  ddh::ReduceArgs red{};
+  red.l[ddh::kNetConv] = {n->part[ddh::kNetConv], n->bpart[ddh::kNetConv], n->grads + nt.hwoff, n->grads + nt.hboff,
+                          batch * ddh::head_strips(n->T), nt.c1, nt.c1, 2, 1, 0};
   for (int i = ddh::kNetConv - 1; i >= 0; --i) {
     const ddh::NetLayer& L = nt.l[i];
     ddh::ConvArgs a = layer_args(n, i);
-    NET_HIP(ddh::launch_conv_wgrad(a, n->dz[i], L.cout, batch, n->part, n->bpart, st));
-    const int groups = ddh::wgrad_partials(a.H, a.W, a.cinp, L.cout, batch);
-    NET_HIP(ddh::launch_wgrad_reduce(n->part, n->bpart, groups, L.cin, L.cinp, L.cout, 9, n->grads + L.woff,
-                                     n->grads + L.boff, st));
+    NET_HIP(ddh::launch_conv_wgrad(a, n->dz[i], L.cout, batch, n->part[i], n->bpart[i], st));
+    red.l[i] = {n->part[i], n->bpart[i], n->grads + L.woff, n->grads + L.boff,
+                ddh::wgrad_partials(a.H, a.W, a.cinp, L.cout, batch), L.cin, L.cinp, L.cout, 9, 0};
     if (i == 0) break;
     // data gradient at the layer input: the same product with flipped weights
     ddh::ConvArgs d{};
@@ -185,6 +191,7 @@ dd_status backward(dd_net* n, int batch, hipStream_t st) {
     }
     NET_HIP(ddh::launch_route(r, batch, st));
   }
+  NET_HIP(ddh::launch_wgrad_reduce(red, st));
   return DD_OK;
 }
 
@@ -282,19 +289,28 @@ dd_status dd_net_create(const dd_net_params* p, dd_net** out) {
     NET_A(n->m, (size_t)n->nparams);
     NET_A(n->v, (size_t)n->nparams);
     const size_t strips = B * ddh::head_strips(n->T);
-    size_t part = strips * 2 * (size_t)n->nt.c1, bpart = strips * 2;   // the head's
+    // gradient partials of all layers in one allocation, the head's last
+    size_t rows[ddh::kNetConv + 1], all = 0;
+    for (int i = 0; i <= ddh::kNetConv; ++i) {
+      const ddh::NetLayer& L = n->nt.l[std::min(i, ddh::kNetConv - 1)];
+      const int H = n->H(L.level);
+      rows[i] = i < ddh::kNetConv ? (size_t)ddh::wgrad_partials(H, H, L.cinp, L.cout, n->B) : strips;
+      all += rows[i] * part_floats(n, i) + rows[i] * bias_floats(n, i);
+    }
+    float* partials = nullptr;
+    NET_A(partials, all);
+    for (int i = 0; partials && i <= ddh::kNetConv; ++i) {
+      n->part[i] = partials;
+      n->bpart[i] = partials += rows[i] * part_floats(n, i);
+      partials += rows[i] * bias_floats(n, i);
+    }
     for (int i = 0; i < ddh::kNetConv; ++i) {
       const ddh::NetLayer& L = n->nt.l[i];
       const int H = n->H(L.level);
       NET_A(n->dz[i], B * H * H * L.cout);
       if (i > 0) NET_A(n->dc[i], B * H * H * L.cin);
-      const size_t groups = ddh::wgrad_partials(H, H, L.cinp, L.cout, n->B);
-      part = std::max(part, groups * 9 * L.cinp * L.cout);
-      bpart = std::max(bpart, groups * L.cout);
     }
     NET_A(n->t, B * T2 * 2);
-    NET_A(n->part, part);
-    NET_A(n->bpart, bpart);
     NET_A(n->loss, strips);
     NET_A(n->den, strips * 2);
     NET_A(n->desc, B);
@@ -484,8 +500,8 @@ dd_status dd_net_gradient(dd_net* n, const float* x, const float* t, const dd_ti
   h.batch = batch;
   h.den = n->den;
   h.dz7 = n->dz[ddh::kNetConv - 1];
-  h.part = n->part;
-  h.bpart = n->bpart;
+  h.part = n->part[ddh::kNetConv];
+  h.bpart = n->bpart[ddh::kNetConv];
   h.loss = n->loss;
   NET_HIP(ddh::launch_head(h, st));
   NET_TRY(backward(n, batch, st));

@@ -26,8 +26,8 @@ struct dd_net {
   ddh::bf16* dz[ddh::kNetConv] = {};
   float* dc[ddh::kNetConv] = {};     // data gradient at the input of layer i (i >= 1)
   float* t = nullptr;
-  float* part = nullptr;
-  float* bpart = nullptr;
+  float* part[ddh::kNetConv + 1] = {};    // gradient partials of each layer, the head last
+  float* bpart[ddh::kNetConv + 1] = {};
   double* loss = nullptr;            // one per strip of a tile
   double* den = nullptr;
   ddh::TileDescDev* desc = nullptr;
