@@ -18,7 +18,8 @@
 // reduction's rounding error, which k^2 near an eigenvalue of one of its pivots raises, shows in the
 // result: over 500 grids of up to 400 intervals the two methods' corrections differ by more
 // than 1e-9 on 5 of 234 at 10 intervals per wavelength and on 23 of 266 at 5.  Results there are held
-// to what they were, so the reduction stays.
+// to what they were, so the reduction stays.  (At 10 the difference is the reduction's error: from residuals in
+// long double over 200 grids, 4e-5 at worst and above 1e-9 on 4, against 4.6e-12 for the dissection.)
 //
 // E_0 is block tridiagonal in the coarse rows (nb = M-1 blocks of n = M-1 unknowns).
 // In the block cyclic reduction, at every level the odd
