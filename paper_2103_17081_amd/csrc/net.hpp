@@ -151,7 +151,6 @@ hipError_t launch_route(const RouteArgs& a, int batch, hipStream_t st);
 hipError_t launch_head(const HeadArgs& a, hipStream_t st);
 hipError_t launch_adam(float* p, const float* g, float* m, float* v, long long n, float lr, float b1, float b2,
                        float eps, float c1, float c2, hipStream_t st);
-hipError_t launch_input_convert(const float* xf, bf16* xb, long long pixels, hipStream_t st);
 hipError_t launch_tiles(const TileArgs& a, int nsub, int nrhs, hipStream_t st);
 hipError_t launch_packed_to_tiles(const SubDesc* subs, int nsub, int nrhs, long long nfine,
                                   const cplx<double>* u, const double* scale, int T, float* t, hipStream_t st);

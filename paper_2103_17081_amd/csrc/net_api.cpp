@@ -100,8 +100,9 @@ void build_table(dd_net* n) {
   n->nfrag = fo;
 }
 
-// Forward product arguments of layer i (input operands from the activations).
-ddh::ConvArgs layer_args(const dd_net* n, int i) {
+// Forward product arguments of layer i (input operands from the activations; the first layer's from the caller's
+// xf if that is set).
+ddh::ConvArgs layer_args(const dd_net* n, int i, const float* xf) {
   const ddh::NetLayer& L = n->nt.l[i];
   ddh::ConvArgs a{};
   a.x0 = L.src0 < 0 ? n->x : n->act[L.src0];
@@ -113,7 +114,8 @@ ddh::ConvArgs layer_args(const dd_net* n, int i) {
   a.cinp = L.cinp;
   a.lc = log2i(a.cinp);
   a.c1 = L.c1;
-  a.mode = L.mode;
+  a.mode = L.src0 < 0 && xf ? ddh::kInput : L.mode;
+  a.xf = xf;
   a.relu = 1;
   a.ksteps = L.ksteps;
   a.nb = L.cout / 16;
@@ -136,14 +138,14 @@ dd_status prepare(dd_net* n, hipStream_t st) {
   return DD_OK;
 }
 
-dd_status backward(dd_net* n, int batch, hipStream_t st) {
+dd_status backward(dd_net* n, int batch, hipStream_t st, const float* xf) {
   const ddh::NetTable& nt = n->nt;
   ddh::ReduceArgs red{};
   red.l[ddh::kNetConv] = {n->part[ddh::kNetConv], n->bpart[ddh::kNetConv], n->grads + nt.hwoff, n->grads + nt.hboff,
                           batch * ddh::head_strips(n->T), nt.c1, nt.c1, 2, 1, 0};
   for (int i = ddh::kNetConv - 1; i >= 0; --i) {
     const ddh::NetLayer& L = nt.l[i];
-    ddh::ConvArgs a = layer_args(n, i);
+    ddh::ConvArgs a = layer_args(n, i, xf);
     NET_HIP(ddh::launch_conv_wgrad(a, n->dz[i], L.cout, batch, n->part[i], n->bpart[i], st));
     red.l[i] = {n->part[i], n->bpart[i], n->grads + L.woff, n->grads + L.boff,
                 ddh::wgrad_partials(a.H, a.W, a.cinp, L.cout, batch), L.cin, L.cinp, L.cout, 9, 0};
@@ -206,12 +208,8 @@ namespace ddh {
 
 dd_status net_forward(dd_net* n, int batch, hipStream_t st, const float* xf, float* y) {
   for (int i = 0; i < kNetConv; ++i) {
-    ConvArgs a = layer_args(n, i);
+    ConvArgs a = layer_args(n, i, xf);
     a.out_bf = n->act[i];
-    if (i == 0 && xf) {
-      a.mode = kInput;
-      a.xf = xf;
-    }
     if (i == kNetConv - 1 && y) {
       a.y = y;
       a.head = n->params + n->nt.hwoff;   // the biases follow the weights
@@ -481,10 +479,9 @@ dd_status dd_net_gradient(dd_net* n, const float* x, const float* t, const dd_ti
       return ddh::fail_msg(DD_EINVAL, "tile description larger than the tile");
   static_assert(sizeof(dd_tile_desc) == sizeof(ddh::TileDescDev), "tile description layout");
   hipStream_t st = (hipStream_t)stream;
-  const long long pix = (long long)batch * n->T * n->T;
+  NET_TRY(ddh::net_forward(n, batch, st, x, nullptr));
+  // from pageable memory: the host's share of the copy runs beside the forward pass
   NET_HIP(hipMemcpyAsync(n->desc, desc, (size_t)batch * sizeof(dd_tile_desc), hipMemcpyHostToDevice, st));
-  NET_HIP(ddh::launch_input_convert(x, n->x, pix, st));
-  NET_TRY(ddh::net_forward(n, batch, st, nullptr, nullptr));
   ddh::HeadArgs h{};
   h.a7 = n->act[ddh::kNetConv - 1];
   h.params = n->params;
@@ -504,7 +501,7 @@ dd_status dd_net_gradient(dd_net* n, const float* x, const float* t, const dd_ti
   h.bpart = n->bpart[ddh::kNetConv];
   h.loss = n->loss;
   NET_HIP(ddh::launch_head(h, st));
-  NET_TRY(backward(n, batch, st));
+  NET_TRY(backward(n, batch, st, x));
   if (grad) NET_HIP(hipMemcpyAsync(grad, n->grads, (size_t)n->nparams * sizeof(float), hipMemcpyDeviceToDevice, st));
   std::vector<double> lp((size_t)batch * ddh::head_strips(n->T));
   NET_HIP(hipMemcpyAsync(lp.data(), n->loss, lp.size() * sizeof(double), hipMemcpyDeviceToHost, st));

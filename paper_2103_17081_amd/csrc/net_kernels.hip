@@ -36,6 +36,13 @@ __device__ __forceinline__ f32x4 mfma(bf16x8 a, bf16x8 b, f32x4 c) {
 __device__ __forceinline__ bf16x8 load_input(const ConvArgs& a, int b, int y, int x, int ch) {
   const int H = a.H, W = a.W;
   if (a.mode == kPlain) return *(const bf16x8*)(a.x0 + (((size_t)b * H + y) * W + x) * a.cinp + ch);
+  if (a.mode == kInput) {
+    const f32x4 v = *(const f32x4*)(a.xf + (((size_t)b * H + y) * W + x) * kNetIn);
+    bf16x8 o = zero8();
+#pragma unroll
+    for (int i = 0; i < kNetIn; ++i) o[i] = (bf16)v[i];
+    return o;
+  }
   if (a.mode == kPool) {
     const int W2 = 2 * W;
     const bf16* base = a.x0 + (((size_t)b * 2 * H + 2 * y) * W2 + 2 * x) * a.cinp + ch;
@@ -939,23 +946,6 @@ hipError_t launch_adam(float* p, const float* g, float* m, float* v, long long n
 }
 
 // ---- tiles ---------------------------------------------------------------------------
-
-__global__ void input_convert_kernel(const float* __restrict__ xf, bf16* __restrict__ xb, long long pixels) {
-  for (long long p = blockIdx.x * (long long)blockDim.x + threadIdx.x; p < pixels;
-       p += (long long)gridDim.x * blockDim.x) {
-    const f32x4 v = *(const f32x4*)(xf + 4 * p);
-    bf16x8 o = zero8();
-#pragma unroll
-    for (int i = 0; i < 4; ++i) o[i] = (bf16)v[i];
-    *(bf16x8*)(xb + 8 * p) = o;
-  }
-}
-
-hipError_t launch_input_convert(const float* xf, bf16* xb, long long pixels, hipStream_t st) {
-  const int blocks = (int)std::min<long long>((pixels + 255) / 256, 8192);
-  hipLaunchKernelGGL(input_convert_kernel, dim3(blocks), dim3(256), 0, st, xf, xb, pixels);
-  return hipGetLastError();
-}
 
 // Network input of solve (rhs, sub) = tile rhs * nsub + sub, from f = R_j r.
 __global__ void __launch_bounds__(kNetThreads) tiles_kernel(TileArgs a) {
