@@ -82,7 +82,7 @@ struct dd_handle {
   std::vector<int> cuts_x, cuts_y;
   std::vector<SubDesc> subs_h;
   long long nfine = 0, ncoarse = 0, nfac = 0;
-  int max_nj = 0, max_nc = 0, max_mx = 0;
+  int max_nj = 0, max_nx = 0, max_nc = 0, max_mx = 0;
   ddh::Consts cs{};
   std::vector<double> pivmin_h;
   // device
@@ -312,6 +312,7 @@ dd_status validate_and_plan(const dd_params* p, dd_handle* h) {
       goff += d.defl == DD_DEFLATION_LINEAR ? ddh::coarse_factor_size(d.mx, d.my)
                                             : ddh::coarse_factor_size_paired(d.bmx, d.bmy);
       h->max_nj = std::max(h->max_nj, d.nx * d.ny);
+      h->max_nx = std::max(h->max_nx, d.nx);
       h->max_nc = std::max(h->max_nc, d.ncp);
       h->max_mx = std::max(h->max_mx, d.mx);
       h->subs_h.push_back(d);
@@ -335,7 +336,7 @@ dd_status check_lds(dd_handle* h) {
   int dev = 0, maxlds = 0;
   DD_HIP(hipGetDevice(&dev));
   DD_HIP(hipDeviceGetAttribute(&maxlds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev));
-  size_t need = h->direct ? ddh::direct_lds_bytes(h->max_nj) : ddh::inner_lds_bytes<T>(h->max_nj, h->max_nc, h->maxit);
+  size_t need = h->direct ? ddh::direct_lds_bytes(h->max_nj, h->max_nx) : ddh::inner_lds_bytes<T>(h->max_nj, h->max_nc, h->maxit);
   if (need > (size_t)maxlds)
     return fail(DD_EINVAL, "subdomain tile too large for LDS (" + std::to_string(need) + " > " +
                                std::to_string(maxlds) + " bytes); use more subdomains or fewer inner iterations");
@@ -422,6 +423,7 @@ ddh::DirectArgs direct_args(dd_handle* h) {
   a.zstride = h->ndof;
   a.nrhs = h->nrhs;
   a.max_nj = h->max_nj;
+  a.max_nx = h->max_nx;
   return a;
 }
 
@@ -531,7 +533,8 @@ dd_status dd_setup(const dd_params* p, void* stream, dd_handle** out) {
     if (h->direct) {
       // twisted block factorisation of every local matrix: its 9-coefficient form, factored by the same
       // kernel as E through per-subdomain views (block size nx, ny block rows)
-      DD_TRY(h->alloc(&h->ffac, (size_t)h->nffac));
+      DD_TRY(h->alloc(&h->ffac, (size_t)h->nffac + ddh::detail::kFactorPad));
+      DD_HIP(hipMemsetAsync(h->ffac + h->nffac, 0, ddh::detail::kFactorPad * sizeof(cplx<double>), st));
       DD_TRY(h->alloc(&h->foff, h->nsub));
       DD_HIP(hipMemcpy(h->foff, h->foff_h.data(), h->nsub * sizeof(long long), hipMemcpyHostToDevice));
       std::vector<SubDesc> views(h->subs_h);
@@ -556,7 +559,7 @@ dd_status dd_setup(const dd_params* p, void* stream, dd_handle** out) {
       if (e != hipSuccess) return fail(DD_EHIP, std::string("direct factorisation: ") + hipGetErrorString(e));
       for (int j = 0; j < h->nsub; ++j)
         DD_TRY(check_pivots("local matrix B_" + std::to_string(j), h->pivmin_h[2 * j], h->pivmin_h[2 * j + 1]));
-      DD_HIP(ddh::configure_direct(h->max_nj));
+      DD_HIP(ddh::configure_direct(h->max_nj, h->max_nx));
     }
     if (h->p.coarse_intervals > 0) {
       h->gc = new ddh::GlobalCoarse();

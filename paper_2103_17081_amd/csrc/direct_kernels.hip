@@ -11,6 +11,8 @@
 // two sweeps side by side.  One workgroup per (subdomain, right-hand side): gather R_j r,
 // the block sweeps with the lower couplings taken from the stencil's row classes, scatter
 // of the owned nodes.
+#include <type_traits>
+
 #include "coarse.hpp"
 #include "kernels.hpp"
 #include "stencil.hpp"
@@ -48,11 +50,27 @@ hipError_t launch_fine_coef(const SubDesc* subs, int nsub, Consts cs, int local_
   return hipGetLastError();
 }
 
-size_t direct_lds_bytes(int max_nj) {
-  return 64 * sizeof(cplx<double>) + 2 * (size_t)max_nj * sizeof(cplx<double>);
+// Forms of the block solve, by the widest tile of the handle: the wave chain (coarse.hpp) with 4 lanes per row
+// (up to 16 nodes wide) or 2 lanes of 13 or 16 columns, else the step-by-step forms.  Up to 32 nodes a solve is a
+// chain of latencies: with two workgroup barriers per block row an application took 24 us for 16
+// subdomains 15 nodes wide and 38 for 27 wide, now 11 and 22 (with stored products instead of couplings, 17 and 27).  Wider blocks do not fit a wave's registers.
+enum DirectForm { kDirectNarrow, kDirectChain, kDirectWide, kDirectSteps };
+
+static size_t direct_lds(int max_nj, bool chain) {
+  return (64 + 2 * (size_t)max_nj + (chain ? lower_entries(max_nj) + detail::kChainScratch : 0)) * sizeof(cplx<double>);
 }
 
-template <int NT>
+// Tall tiles whose couplings do not fit beside the vectors keep the step-by-step forms.
+static DirectForm direct_form(int max_nj, int max_nx) {
+  if (max_nx > 32 || direct_lds(max_nj, true) > 160 * 1024) return kDirectSteps;
+  return max_nx <= 16 ? kDirectNarrow : (max_nx <= 26 ? kDirectChain : kDirectWide);
+}
+
+size_t direct_lds_bytes(int max_nj, int max_nx) {
+  return direct_lds(max_nj, direct_form(max_nj, max_nx) != kDirectSteps);
+}
+
+template <int NT, int Form>
 __global__ void __launch_bounds__(NT) direct_solve_kernel(DirectArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int sidx = a.order ? a.order[blockIdx.x] : (int)blockIdx.x;
@@ -81,10 +99,32 @@ __global__ void __launch_bounds__(NT) direct_solve_kernel(DirectArgs a) {
     return tab[cls * kStencilPts + (e == 0 ? kSW : kS)];
   };
   const cplx<double>* __restrict__ F = a.ffac + a.foff[sub];
-  // the two halves of the workgroup run the two sweeps of the twisted factorisation; for
-  // 33..64-wide tiles the factor entries of one step are loaded at a time (179 us per
-  // application on the large workload, against 189 and 193 us with 2 and 3 steps ahead)
+  if constexpr (Form != kDirectSteps) {
+    // couplings of every node to the row below, as the chain reads them: zeros where they leave the row
+    cplx<double>* scratch = x + a.max_nj;
+    cplx<double>* lc = scratch + detail::kChainScratch;
+    using Chain = std::conditional_t<Form == kDirectNarrow, detail::CoarseChain<NT, 4, 4, 6>,
+                                     std::conditional_t<Form == kDirectChain, detail::CoarseChain<NT, 2, 13, 3>,
+                                                        detail::CoarseChain<NT, 2, 16, 2>>>;
+    Chain chain;
+    chain.start(nx, ny, F);
+    for (int n = tid; n < nj; n += NT) {
+      const int i = n / nx, c = n - i * nx;
+      lc[3 * n] = c > 0 ? lower(i, c, 0) : czero<double>();
+      lc[3 * n + 1] = lower(i, c, 1);
+      lc[3 * n + 2] = czero<double>();
+    }
+    if (tid == 0) lc[3 * nj] = czero<double>();
+    __syncthreads();
+    chain.solve(F, lc, t, x, scratch);
+  } else
+  // The two halves of the workgroup run the two sweeps of the twisted factorisation.  Up to 48 nodes wide the
+  // entries of two steps are loaded together, which hides part of their latency (16 subdomains of 35 nodes:
+  // 81 us one step at a time, 65 two, 66 three; 40 nodes: 86 two, 94 three); wider tiles stream
+  // their factors and are faster one step at a time (53 nodes, 256 subdomains: 179 us against 189 and 193).
   if (nx <= 32) detail::twisted_solve_ring<8, 4, 8, NT / 2>(nx, ny, F, lower, t, x);
+  else if (nx <= 40) detail::twisted_solve_ring<4, 10, 2, NT / 2>(nx, ny, F, lower, t, x);
+  else if (nx <= 48) detail::twisted_solve_ring<4, 12, 2, NT / 2>(nx, ny, F, lower, t, x);
   else if (nx <= 64) detail::twisted_solve_ring<4, 16, 1, NT / 2>(nx, ny, F, lower, t, x);
   else detail::twisted_solve_plain<NT / 2>(nx, ny, F, lower, t, x);
   for (int n = tid; n < nj; n += NT) {
@@ -111,16 +151,27 @@ __global__ void __launch_bounds__(NT) direct_solve_kernel(DirectArgs a) {
   }
 }
 
+typedef void (*DirectKernel)(DirectArgs);
+
+static DirectKernel direct_kernel(int max_nj, int max_nx) {
+  switch (direct_form(max_nj, max_nx)) {
+    case kDirectNarrow: return direct_solve_kernel<kInnerThreads, kDirectNarrow>;
+    case kDirectChain: return direct_solve_kernel<kInnerThreads, kDirectChain>;
+    case kDirectWide: return direct_solve_kernel<kInnerThreads, kDirectWide>;
+    default: return direct_solve_kernel<kInnerThreads, kDirectSteps>;
+  }
+}
+
 hipError_t launch_direct_solve(const DirectArgs& a, hipStream_t st) {
   const int nblocks = a.cs.nsub * a.nrhs;
-  hipLaunchKernelGGL(direct_solve_kernel<kInnerThreads>, dim3(nblocks), dim3(kInnerThreads),
-                     direct_lds_bytes(a.max_nj), st, a);
+  hipLaunchKernelGGL(direct_kernel(a.max_nj, a.max_nx), dim3(nblocks), dim3(kInnerThreads), direct_lds_bytes(a.max_nj, a.max_nx),
+                     st, a);
   return hipGetLastError();
 }
 
-hipError_t configure_direct(int max_nj) {
-  return hipFuncSetAttribute((const void*)direct_solve_kernel<kInnerThreads>,
-                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)direct_lds_bytes(max_nj));
+hipError_t configure_direct(int max_nj, int max_nx) {
+  return hipFuncSetAttribute((const void*)direct_kernel(max_nj, max_nx), hipFuncAttributeMaxDynamicSharedMemorySize,
+                             (int)direct_lds_bytes(max_nj, max_nx));
 }
 
 }  // namespace ddh

@@ -164,12 +164,14 @@ struct DirectArgs {
   const int* jdev;
   long long rslot, zslot;
   int nrhs, max_nj;
+  int max_nx;                    // widest row
 };
 hipError_t launch_fine_coef(const SubDesc* subs, int nsub, Consts cs, int local_bc, cplx<double>* Bc,
                             hipStream_t st);
 hipError_t launch_direct_solve(const DirectArgs& a, hipStream_t st);
-size_t direct_lds_bytes(int max_nj);
-hipError_t configure_direct(int max_nj);
+// max_nj, max_nx: most nodes and widest row of the handle's tiles
+size_t direct_lds_bytes(int max_nj, int max_nx);
+hipError_t configure_direct(int max_nj, int max_nx);
 
 // ---- static device scratch (the entry point that allocates nothing) -----------------
 // Device address on the current device, and size, of the library's static scratch array
