@@ -52,8 +52,9 @@ hipError_t launch_fine_coef(const SubDesc* subs, int nsub, Consts cs, int local_
 
 // Forms of the block solve, by the widest tile of the handle: the wave chain (coarse.hpp) with 4 lanes per row
 // (up to 16 nodes wide) or 2 lanes of 13 or 16 columns, else the step-by-step forms.  Up to 32 nodes a solve is a
-// chain of latencies: with two workgroup barriers per block row an application took 24 us for 16
-// subdomains 15 nodes wide and 38 for 27 wide, now 11 and 22 (with stored products instead of couplings, 17 and 27).  Wider blocks do not fit a wave's registers.
+// chain of latencies: with two workgroup barriers per block row an application took 21 us for 16 subdomains
+// 15 nodes wide and 38 for 27 wide, now 11 and 22 (16 and 27 with stored products instead of couplings, twice
+// the bytes).  Wider blocks do not fit a wave's registers.
 enum DirectForm { kDirectNarrow, kDirectChain, kDirectWide, kDirectSteps };
 
 static size_t direct_lds(int max_nj, bool chain) {
