@@ -125,6 +125,12 @@ __device__ __forceinline__ int fresh_tid() {
   return t;
 }
 
+// Node that thread `tid` loads where the strided loop over a vector of nj nodes has it at n: n itself, or past
+// the end, where the value is dropped, a node that its own wave has written.  (Another wave's may still
+// be on its way to memory, and a dropped value is multiplied by zero, which what the memory held
+// before, a NaN, would survive.)  Needs a wave with a node of its own.
+__host__ __device__ inline int sweep_node(int n, int tid, int nj) { return n < nj ? n : (tid < nj ? tid : nj - 1); }
+
 // ---- wavefront / workgroup reductions ------------------------------------
 // DPP row operations (16-lane rows): swap adjacent lanes, swap lane pairs, mirror
 // within each half row, mirror within the row.  Applied in this order with adds,

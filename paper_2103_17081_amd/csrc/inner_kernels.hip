@@ -327,8 +327,8 @@ __device__ __forceinline__ double tile_norm(const SubDesc& d, const cplx<T>* v, 
 // by the latency of the basis loads, so a thread issues the loads of its next node before it
 // works on the current one: `load(buf, n)` issues one node's loads, `use(buf, n, valid)` works on
 // them, `put(n)` stores the results, after the next loads were issued.  Every path issues the
-// same number of loads (nodes past the end are clamped and their results dropped): the
-// wait before `use` then covers that node's loads only.
+// same number of loads (past the end those of sweep_node, whose results are dropped): the
+// wait before `use` then covers that node's loads only.  Waves past the end have nothing to do.
 template <typename T, int Count>
 struct SweepBuf {
   cplx<T> v[Count > 0 ? Count : 1], u;
@@ -337,20 +337,21 @@ struct SweepBuf {
 template <typename T, int NT, int Count, typename Load, typename Use, typename Put>
 __device__ __forceinline__ void sweep_nodes(int nj, Load load, Use use, Put put) {
   const int tid = fresh_tid(), steps = (nj + NT - 1) / NT;
+  if (__builtin_amdgcn_readfirstlane(tid) >= nj) return;
   SweepBuf<T, Count> b0, b1;
-  load(b0, min(tid, nj - 1));
+  load(b0, sweep_node(tid, tid, nj));
   for (int e = 0; e + 1 < steps; e += 2) {
     const int n0 = tid + e * NT, n1 = n0 + NT;
-    load(b1, min(n1, nj - 1));
+    load(b1, sweep_node(n1, tid, nj));
     use(b0, n0, true);
-    load(b0, min(n1 + NT, nj - 1));
+    load(b0, sweep_node(n1 + NT, tid, nj));
     put(n0);
-    use(b1, min(n1, nj - 1), n1 < nj);
+    use(b1, sweep_node(n1, tid, nj), n1 < nj);
     if (n1 < nj) put(n1);
   }
   if (steps & 1) {
     const int n = tid + (steps - 1) * NT;
-    use(b0, min(n, nj - 1), n < nj);
+    use(b0, sweep_node(n, tid, nj), n < nj);
     if (n < nj) put(n);
   }
 }
