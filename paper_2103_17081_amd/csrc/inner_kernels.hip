@@ -63,14 +63,24 @@ struct Lds {
   double* cs;          // Givens cosines (maxit)
   double* scal;        // 8 scalars
   int* ctrl;           // 4 ints
+  cplx<double>* chain; // scratch of the coarse solve
   int stride;          // maxit + 2
 };
 
-// Tile A also serves as the coarse solve's scratch (the tile is rewritten by the prolongation).
+// Place of the coarse solve's scratch: tile A (rewritten by the prolongation), or where tile A is smaller, the
+// products cv (free until the operator is applied) if they are long enough, so that only short
+// bases of small tiles need extra room.
+constexpr size_t kChainBytes = detail::kChainScratch * sizeof(cplx<double>);
+
 template <typename T>
-__host__ __device__ size_t tile_a_bytes(int max_nj) {
-  const size_t tile = align16((size_t)max_nj * sizeof(cplx<T>)), scratch = detail::kChainScratch * sizeof(cplx<double>);
-  return tile > scratch ? tile : scratch;
+__host__ __device__ bool scratch_in_cv(int max_nj, int maxit) {
+  return (size_t)max_nj * sizeof(cplx<T>) < kChainBytes && maxit + 2 >= detail::kChainScratch;
+}
+
+template <typename T>
+__host__ __device__ size_t tile_a_bytes(int max_nj, int maxit) {
+  const size_t tile = align16((size_t)max_nj * sizeof(cplx<T>));
+  return tile >= kChainBytes || scratch_in_cv<T>(max_nj, maxit) ? tile : kChainBytes;
 }
 
 // The coarse vectors and the sums' wave partials share their place: the ones live within an
@@ -86,7 +96,7 @@ template <typename T>
 __host__ __device__ size_t lds_bytes(int max_nj, int max_nc, int maxit, int nt) {
   const size_t s = (size_t)maxit + 2;
   size_t b = 0;
-  b += tile_a_bytes<T>(max_nj) + align16((size_t)max_nj * sizeof(cplx<T>));
+  b += tile_a_bytes<T>(max_nj, maxit) + align16((size_t)max_nj * sizeof(cplx<T>));
   b += align16(kClasses * kStencilPts * sizeof(cplx<T>));
   b += coarse_or_partials_bytes<T>(max_nc, maxit, nt);
   b += 2 * align16(s * sizeof(cplx<T>));
@@ -105,7 +115,7 @@ __device__ Lds<T> carve(unsigned char* base, int max_nj, int max_nc, int maxit) 
   L.stride = (int)s;
   size_t o = 0;
   auto take = [&](size_t bytes) { unsigned char* p = base + o; o += align16(bytes); return p; };
-  L.A = (cplx<T>*)take(tile_a_bytes<T>(max_nj));
+  L.A = (cplx<T>*)take(tile_a_bytes<T>(max_nj, maxit));
   L.B = (cplx<T>*)take((size_t)max_nj * sizeof(cplx<T>));
   L.tab = (cplx<T>*)take(kClasses * kStencilPts * sizeof(cplx<T>));
   L.ct = (cplx<double>*)take(coarse_or_partials_bytes<T>(max_nc, maxit, NT));
@@ -122,6 +132,7 @@ __device__ Lds<T> carve(unsigned char* base, int max_nj, int max_nc, int maxit) 
   L.cs = (double*)take(s * sizeof(double));
   L.scal = (double*)take(8 * sizeof(double));
   L.ctrl = (int*)take(4 * sizeof(int));
+  L.chain = scratch_in_cv<T>(max_nj, maxit) ? L.cv : (cplx<double>*)L.A;
   return L;
 }
 
@@ -269,7 +280,7 @@ __device__ __forceinline__ void prolong_to(const SubDesc& d, const cplx<double>*
 template <typename T, int NT, int Kind>
 __device__ __forceinline__ void deflated_op(const SubDesc& d, const cplx<double>* fac, Lds<T>& L, bool apply,
                                             cplx<double>* keep) {
-  coarse_solve<NT, Kind>(d, fac, L.lc, L.ct, L.ca, reinterpret_cast<cplx<double>*>(L.A), [&]() {
+  coarse_solve<NT, Kind>(d, fac, L.lc, L.ct, L.ca, L.chain, [&]() {
     if (apply) {
       apply_B<T, false>(d, L.tab, L.A, L.B);
       lds_barrier();
