@@ -128,9 +128,10 @@ typedef struct {
   /* Algorithmic bytes of the subdomain-solve kernel summed over its launches: per solve,
      gather 16 n_j + scatter 16 owned_j (32 when the two-level correction is added) +
      (k_j + 1) coarse-factor reads of 16 (my mx^2 + 3 mx my) bytes + the coarse vectors kept for the
-     recovery 16 nc (2 k_j + 2) + Krylov traffic s n_j (1 + 3 k_j + k_j (k_j + 1)) when
-     k_j > 0 (basis writes 1 + 2 k_j, two sweeps per iteration reading k_j (k_j + 1) basis
-     vectors in all, final combination k_j) + local rhs write/read
+     recovery 16 nc (2 k_j + 2) + Krylov traffic s n_j (1 + 3 k_j + k_j (k_j + 1) + l_j (l_j + 1) / 2)
+     when k_j > 0 (basis writes 1 + 2 k_j, two sweeps per iteration reading k_j (k_j + 1) basis
+     vectors in all, the later ones of a basis of more than b = 16 (FP32) or 8 vectors once more,
+     l_j = max(0, k_j - 1 - b), final combination k_j) + local rhs write/read
      2 s n_j, with s = 8 (FP32) or 16 bytes per complex value. */
   double inner_bytes;
   /* The two basis sweeps of the outer delayed CGS2 (events around each launch):

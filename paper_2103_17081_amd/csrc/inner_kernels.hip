@@ -934,9 +934,11 @@ __device__ __forceinline__ void inner_solve(const InnerArgs<T>& a, unsigned char
       const unsigned long long own = (unsigned long long)(d.oi1 - d.oi0 + 1) * (d.oj1 - d.oj0 + 1);
       const unsigned long long fac_bytes = 16ull * (unsigned long long)coarse_solve_values(d);
       const unsigned long long ncp = (unsigned long long)d.ncp;
+      // the update sweep of step j reads the vectors after its first kSweepVecs once more
+      const unsigned long long late = k > kSweepVecs<T> + 1 ? (unsigned long long)(k - 1 - kSweepVecs<T>) : 0ull;
       unsigned long long bytes = 16ull * nn + (a.zadd ? 32ull : 16ull) * own +
                                  (kk + 1) * fac_bytes + 16ull * ncp * (2 * kk + 2) +
-                                 (kk ? s * nn * (1 + 3 * kk + kk * (kk + 1)) : 0ull) + 2 * s * nn;
+                                 (kk ? s * nn * (1 + 3 * kk + kk * (kk + 1) + late * (late + 1) / 2) : 0ull) + 2 * s * nn;
       if (offered) bytes += fac_bytes + (a.gtile ? 8ull : s) * nn + 3 * s * nn + 32ull * ncp;
       atomicAdd(a.counters + 4, bytes);
     }

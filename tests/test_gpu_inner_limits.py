@@ -1,4 +1,5 @@
-"""Subdomain GMRES on the smallest tiles with the longest bases that fit in LDS, against the oracle.
+"""Subdomain GMRES at the limits of its bases: the smallest tiles with the longest bases that fit in LDS, against
+the oracle, and the byte count of bases longer than an update sweep holds.
 
 Tiles of 2 x 2 to 3 x 3 nodes are smaller than the coarse solve's scratch: the scratch then lies in another
 vector of the solve (62 iterations and more) or takes extra room (61).  652 and 968 are the largest iteration limits
@@ -43,3 +44,23 @@ def test_smallest_tiles_longest_bases(torch, prec, maxit):
         assert abs(int(it) - itr) <= 1
         if it == itr:
             assert np.linalg.norm(ug - ur) <= (1e-8 if prec == 64 else 2e-3) * np.linalg.norm(ur)
+
+
+@pytest.mark.parametrize("prec,maxit", [(64, 8), (64, 9), (64, 10), (64, 40), (32, 17), (32, 18), (32, 40)])
+def test_bytes_of_long_bases(torch, prec, maxit):
+    """The byte count of one subdomain solve (one subdomain, one outer step) that runs to its iteration limit, below and above
+    the number of vectors (8, complex64 16) that the update sweep keeps for the next step's products."""
+    from paper_2103_17081_amd.binding import Solver
+    print("case: bytes of long bases", prec, maxit, flush=True)
+    with Solver(30.0, n_intervals=24, cuts_x=[0, 24], cuts_y=[0, 24], inner_precision=prec, inner_tol=1e-12,
+                inner_maxit=maxit, outer_maxit=1) as gpu:
+        nx, ny, mx, my = (int(gpu.layout[0, c]) for c in (2, 3, 8, 9))
+        f = crandn(np.random.default_rng(3), nx * ny)
+        _, st = gpu.solve(to_gpu(torch, f))
+    n, nc, k, s = nx * ny, mx * my, maxit, 8 if prec == 32 else 16
+    assert st["precond_applies"] == 1 and st["inner_iters_total"] == k
+    held = 16 if prec == 32 else 8
+    basis_reads = sum((j + 1) + (j + 1) + max(0, j - held) for j in range(k))
+    want = (16 * n + 16 * n + 16 * (k + 1) * (my * mx * mx + 3 * mx * my) + 16 * nc * (2 * k + 2) +
+            s * n * (1 + 3 * k + basis_reads) + 2 * s * n)
+    assert st["inner_bytes"] == want
