@@ -30,6 +30,8 @@
 // block rows), through the same set-up kernel.
 #pragma once
 
+#include <type_traits>
+
 #include "common.hpp"
 
 namespace ddh {
@@ -127,10 +129,11 @@ __device__ __forceinline__ cplx<double> tw_couple(int mx, Lower lower, int i, in
 // operations in order, so nothing has to be waited for).
 __device__ __forceinline__ void wave_lds_order() { asm volatile("" ::: "memory"); }
 
-// Sum of v over the lanes l, l + 64 / L, l + 2 * 64 / L, ... (L = 2 or 4); all of them get it.
+// Sum of v over the lanes l, l + 64 / L, l + 2 * 64 / L, ... (L = 2, 4 or 8); all of them get it.
 template <int L>
 __device__ __forceinline__ double column_sum(double v) {
-  if constexpr (L == 4) v = fold16(v, v);
+  if constexpr (L == 8) v += dpp_f64<kDppRowRor8>(v);
+  if constexpr (L >= 4) v = fold16(v, v);
   return fold32(v, v);
 }
 
@@ -213,14 +216,19 @@ struct CoarseChain {
   struct Inputs {
     cplx<double> k[3], rhs;
   };
-  __device__ __forceinline__ Inputs fetch(const cplx<double>* lc, int i, int dir, const cplx<double>* rhs) const {
-    // lower couplings of row i, or those of row i + 1 transposed; the ones that leave the row are
-    // stored zeros (the last entry is stage_lower's padding)
-    const cplx<double>* e = lc + 3 * (min(i + (dir > 0 ? 1 : 0), my - 1) * mx + r);
+  template <typename Lower>
+  __device__ __forceinline__ Inputs fetch(Lower lower, int i, int dir, const cplx<double>* rhs) const {
     Inputs in;
-    in.k[0] = e[dir > 0 ? -1 : 0];
-    in.k[1] = e[1];
-    in.k[2] = e[dir > 0 ? 3 : 2];
+    if constexpr (std::is_pointer_v<Lower>) {
+      // lower couplings of row i, or those of row i + 1 transposed; the ones that leave the row are
+      // stored zeros (the last entry is stage_lower's padding)
+      const cplx<double>* e = lower + 3 * (min(i + (dir > 0 ? 1 : 0), my - 1) * mx + r);
+      in.k[0] = e[dir > 0 ? -1 : 0];
+      in.k[1] = e[1];
+      in.k[2] = e[dir > 0 ? 3 : 2];
+    } else {
+      tw_couplings(mx, lower, dir > 0 ? min(i, my - 2) : i, r, dir, in.k);
+    }
     in.rhs = rhs[i * mx + r];
     return in;
   }
@@ -261,7 +269,9 @@ struct CoarseChain {
     return cplx<double>{column_sum<L>(acc0.re), column_sum<L>(acc0.im)};
   }
 
-  __device__ __forceinline__ void solve(const cplx<double>* __restrict__ F, const cplx<double>* lc, cplx<double>* t,
+  // `lc`: the couplings staged by stage_lower, or a function lower(i, c, e) as above.
+  template <typename Lower>
+  __device__ __forceinline__ void solve(const cplx<double>* __restrict__ F, Lower lc, cplx<double>* t,
                                         cplx<double>* a, cplx<double>* scratch) {
     const bool writes = threadIdx.x % kWave < mx && g == 0;
     cplx<double>* xb = scratch + half * 32;
@@ -292,7 +302,10 @@ struct CoarseChain {
     // the middle row, by the wave that owns it
     if (!half && count > 0 && first + count - 1 == p) {
       cplx<double> v = t[p * mx + r];
-      auto lower = [lc, this](int i, int c, int e) { return lc[3 * (i * mx + c) + e]; };
+      auto lower = [lc, this](int i, int c, int e) {
+        if constexpr (std::is_pointer_v<Lower>) return lc[3 * (i * mx + c) + e];
+        else return lc(i, c, e);
+      };
       if (p > 0) v = tw_couple(mx, lower, p, r, -1, v, a + (p - 1) * mx);
       if (p < my - 1) v = tw_couple(mx, lower, p, r, 1, v, a + (p + 1) * mx);
       const int km = (count - 1) % Slots;
@@ -334,7 +347,7 @@ struct CoarseChain {
 //   s < nf = my - 1 - p:  a_s (top, if s < p) and a_{my-1-s} (bottom);
 //   s = nf:               y_p;
 //   s > nf:               y_{p-1-(s-nf-1)} (top) and y_{p+1+(s-nf-1)} (bottom).
-// A step forms the coupled right-hand side in `t` once per unknown, then the block product.
+// A step forms the coupled right-hand side, then the block product.
 
 // Block row of half h at step s, or -1.
 __device__ __forceinline__ int tw_step_row(int h, int s, int p, int my) {
@@ -345,71 +358,79 @@ __device__ __forceinline__ int tw_step_row(int h, int s, int p, int my) {
   return i >= 0 && i < my ? i : -1;
 }
 
-// Coupled right-hand side of unknown c of row i at step s, into t.
+// Coupled right-hand side of unknown c of row i at step s.
 template <typename Lower>
-__device__ __forceinline__ void tw_step_rhs(int mx, int my, int p, Lower lower, int h, int s, int i, int c,
-                                            cplx<double>* t, const cplx<double>* a) {
+__device__ __forceinline__ cplx<double> tw_step_rhs(int mx, int my, int p, Lower lower, int h, int s, int i, int c,
+                                                    const cplx<double>* t, const cplx<double>* a) {
   const int nf = my - 1 - p;
   if (s <= nf) {
     cplx<double> v = t[i * mx + c];
     if (i <= p && i > 0) v = tw_couple(mx, lower, i, c, -1, v, a + (i - 1) * mx);
     if (i >= p && i < my - 1) v = tw_couple(mx, lower, i, c, 1, v, a + (i + 1) * mx);
-    t[i * mx + c] = v;
-  } else {
-    const int dir = h == 0 ? 1 : -1;
-    t[i * mx + c] = czero<double>() - tw_couple(mx, lower, i, c, dir, czero<double>(), a + (i + dir) * mx);
+    return v;
   }
+  const int dir = h == 0 ? 1 : -1;
+  return czero<double>() - tw_couple(mx, lower, i, c, dir, czero<double>(), a + (i + dir) * mx);
 }
 
-// Factor blocks of Depth consecutive steps are loaded together into registers (clamped
-// indices, straight-line code) before those steps run.  Lane l of row group r of a half
-// owns columns l + q L, q < Q (mx <= L Q, rows Half / L >= mx).
-template <int L, int Q, int Depth, int Half, typename Lower>
+// The lanes of a wave own 64 / L consecutive rows, so a lane group's load of a column is contiguous; group l
+// owns columns l + q L, q < Q (mx <= L Q, rows Half / L >= mx).  The next step's factor block is loaded into the
+// registers that a step's product has just read.  With `own` (64 entries per wave; mx <= 64) every
+// wave forms the coupled right-hand side for itself, a lane per unknown, which leaves one barrier per step;
+// without, the half forms it in t, with a barrier of its own.
+// Bound by latency with few subdomains (a step is the wait for its factors, the sum over the lane groups and
+// the barrier), by the factor bytes with many.  Exact solves (Own), us per application, lanes of a row next to each other
+// (four columns at a stride of one column: up to 1.5 times the time where mx is a multiple of 8), two barriers and the loads
+// of a step at its start -> this: 4 subdomains of 49 nodes 126 -> 81, 64 of 48 nodes 138 -> 76, 64 of 61
+// nodes 176 -> 130, 256 of 45 nodes 121 -> 112.  Two blocks ahead: the same above 40 nodes, 4 us more below.
+template <int L, int Q, int Half, bool Own, typename Lower>
 __device__ __forceinline__ void twisted_solve_ring(int mx, int my, const cplx<double>* __restrict__ F, Lower lower,
-                                                   cplx<double>* t, cplx<double>* a) {
+                                                   cplx<double>* t, cplx<double>* a, cplx<double>* own = nullptr) {
+  constexpr int kRows = kWave / L;
   const int mm = mx * mx, p = twist_row(my), nf = my - 1 - p, nsteps = 2 * nf + 1;
-  const int h = threadIdx.x / Half, ht = threadIdx.x % Half;
-  const int r = ht / L, l = ht % L;
+  const int h = threadIdx.x / Half, ht = threadIdx.x % Half, lane = threadIdx.x % kWave;
+  const int r = ht / kWave * kRows + lane % kRows, l = lane / kRows;
   const bool active = r < mx;
-  // Columns a lane does not own read column 0 with a zero factor entry, so every step
-  // reads its operands without branches (adding 0 * x leaves the sum unchanged).
+  // Columns past the row read entry 0 of the block and multiply it by 0, so every step reads its
+  // operands without branches (adding 0 * x leaves the sum unchanged).
   int col[Q], eoff[Q];
   bool ok[Q];
 #pragma unroll
   for (int q = 0; q < Q; ++q) {
     ok[q] = active && l + q * L < mx;
-    col[q] = ok[q] ? l + q * L : 0;
+    col[q] = Own || ok[q] ? l + q * L : 0;
     eoff[q] = ok[q] ? col[q] * mx + r : 0;
   }
-  cplx<double> ring[Depth][Q];
-  for (int s0 = 0; s0 < nsteps; s0 += Depth) {
+  if (Own) own += threadIdx.x / kWave * kWave;
+  cplx<double> G[Q];
+  auto load = [&](int s) {
+    const cplx<double>* B = F + (size_t)max(tw_step_row(h, s, p, my), 0) * mm;
 #pragma unroll
-    for (int u = 0; u < Depth; ++u) {
-      const int blk = max(tw_step_row(h, s0 + u, p, my), 0);
-#pragma unroll
-      for (int q = 0; q < Q; ++q) {
-        const cplx<double> fv = F[(size_t)blk * mm + eoff[q]];
-        ring[u][q].re = ok[q] ? fv.re : 0.0;
-        ring[u][q].im = ok[q] ? fv.im : 0.0;
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < Depth; ++u) {
-      const int s = s0 + u;
-      if (s >= nsteps) break;
-      const int i = tw_step_row(h, s, p, my);
-      if (i >= 0 && ht < mx) tw_step_rhs(mx, my, p, lower, h, s, i, ht, t, a);
-      lds_barrier();
-      cplx<double> acc = czero<double>();
-      if (i >= 0) {
-#pragma unroll
-        for (int q = 0; q < Q; ++q) acc = cfma(ring[u][q], t[i * mx + col[q]], acc);
-      }
-      acc.re = row_sum<L>(acc.re);
-      acc.im = row_sum<L>(acc.im);
-      if (i >= 0 && active && l == 0) a[i * mx + r] = s <= nf ? acc : a[i * mx + r] - acc;
+    for (int q = 0; q < Q; ++q) G[q] = B[eoff[q]];
+  };
+  load(0);
+  for (int s = 0; s < nsteps; ++s) {
+    const int i = tw_step_row(h, s, p, my);
+    const cplx<double>* x = t + i * mx;
+    if constexpr (Own) {
+      wave_lds_order();
+      if (i >= 0) own[lane] = lane < mx ? tw_step_rhs(mx, my, p, lower, h, s, i, lane, t, a) : czero<double>();
+      wave_lds_order();
+      x = own;
+    } else {
+      if (i >= 0 && ht < mx) t[i * mx + ht] = tw_step_rhs(mx, my, p, lower, h, s, i, ht, t, a);
       lds_barrier();
     }
+    cplx<double> acc = czero<double>();
+    if (i >= 0) {
+#pragma unroll
+      for (int q = 0; q < Q; ++q) acc = cfma(G[q], Own ? x[col[q]] : keep_c(ok[q], x[col[q]]), acc);
+    }
+    load(s + 1);
+    acc.re = column_sum<L>(acc.re);
+    acc.im = column_sum<L>(acc.im);
+    if (i >= 0 && active && l == 0) a[i * mx + r] = s <= nf ? acc : a[i * mx + r] - acc;
+    lds_barrier();
   }
 }
 
@@ -432,7 +453,7 @@ __device__ __forceinline__ void twisted_solve_plain(int mx, int my, const cplx<d
   };
   for (int s = 0; s < nsteps; ++s) {
     const int i = tw_step_row(h, s, p, my);
-    if (i >= 0 && ht < mx) tw_step_rhs(mx, my, p, lower, h, s, i, ht, t, a);
+    if (i >= 0 && ht < mx) t[i * mx + ht] = tw_step_rhs(mx, my, p, lower, h, s, i, ht, t, a);
     lds_barrier();
     cplx<double> acc = czero<double>();
     if (i >= 0 && active)
@@ -531,8 +552,8 @@ __device__ __forceinline__ void coarse_solve(const SubDesc& d, const cplx<double
     }
     auto lower = [lc, mx = d.mx](int i, int c, int e) { return lc[3 * (i * mx + c) + e]; };
     if (d.mx <= 32) {
-      if constexpr (NT >= 512) detail::twisted_solve_ring<8, 4, 3, NT / 2>(d.mx, d.my, F, lower, t, a);
-      else detail::twisted_solve_ring<4, 8, 3, NT / 2>(d.mx, d.my, F, lower, t, a);
+      if constexpr (NT >= 512) detail::twisted_solve_ring<8, 4, NT / 2, false>(d.mx, d.my, F, lower, t, a);
+      else detail::twisted_solve_ring<4, 8, NT / 2, false>(d.mx, d.my, F, lower, t, a);
     } else {
       detail::twisted_solve_plain<NT / 2>(d.mx, d.my, F, lower, t, a);
     }

@@ -55,21 +55,30 @@ hipError_t launch_fine_coef(const SubDesc* subs, int nsub, Consts cs, int local_
 // chain of latencies: with two workgroup barriers per block row an application took 21 us for 16 subdomains
 // 15 nodes wide and 38 for 27 wide, now 11 and 22 (16 and 27 with stored products instead of couplings, twice
 // the bytes).  Wider blocks do not fit a wave's registers.
-enum DirectForm { kDirectNarrow, kDirectChain, kDirectWide, kDirectSteps };
+enum DirectForm { kDirectNarrow, kDirectChain, kDirectWide, kDirectTall, kDirectSteps, kDirectTight };
+constexpr int kOwnEntries = kInnerThreads;   // a vector of 64 entries per wave
 
-static size_t direct_lds(int max_nj, bool chain) {
-  return (64 + 2 * (size_t)max_nj + (chain ? lower_entries(max_nj) + detail::kChainScratch : 0)) * sizeof(cplx<double>);
+static size_t direct_lds(int max_nj, DirectForm form) {
+  const size_t extra = form == kDirectTight   ? 0
+                       : form == kDirectSteps ? kOwnEntries
+                       : form == kDirectTall  ? detail::kChainScratch
+                                              : lower_entries(max_nj) + detail::kChainScratch;
+  return (64 + 2 * (size_t)max_nj + extra) * sizeof(cplx<double>);
 }
 
-// Tall tiles whose couplings do not fit beside the vectors keep the step-by-step forms.
+// Tall tiles whose couplings do not fit beside the vectors form them as they go (19 x 127 nodes, 8 subdomains:
+// 90 us, step by step 112).  The largest tiles leave no room for a vector per wave.
 static DirectForm direct_form(int max_nj, int max_nx) {
-  if (max_nx > 32 || direct_lds(max_nj, true) > 160 * 1024) return kDirectSteps;
-  return max_nx <= 16 ? kDirectNarrow : (max_nx <= 26 ? kDirectChain : kDirectWide);
+  constexpr size_t kMost = 160 * 1024;
+  if (max_nx <= 32) {
+    if (direct_lds(max_nj, kDirectChain) <= kMost)
+      return max_nx <= 16 ? kDirectNarrow : (max_nx <= 26 ? kDirectChain : kDirectWide);
+    if (direct_lds(max_nj, kDirectTall) <= kMost) return kDirectTall;
+  }
+  return direct_lds(max_nj, kDirectSteps) <= kMost ? kDirectSteps : kDirectTight;
 }
 
-size_t direct_lds_bytes(int max_nj, int max_nx) {
-  return direct_lds(max_nj, direct_form(max_nj, max_nx) != kDirectSteps);
-}
+size_t direct_lds_bytes(int max_nj, int max_nx) { return direct_lds(max_nj, direct_form(max_nj, max_nx)); }
 
 template <int NT, int Form>
 __global__ void __launch_bounds__(NT) direct_solve_kernel(DirectArgs a) {
@@ -100,7 +109,11 @@ __global__ void __launch_bounds__(NT) direct_solve_kernel(DirectArgs a) {
     return tab[cls * kStencilPts + (e == 0 ? kSW : kS)];
   };
   const cplx<double>* __restrict__ F = a.ffac + a.foff[sub];
-  if constexpr (Form != kDirectSteps) {
+  if constexpr (Form == kDirectTall) {
+    detail::CoarseChain<NT, 2, 16, 2> chain;
+    chain.start(nx, ny, F);
+    chain.solve(F, lower, t, x, x + a.max_nj);
+  } else if constexpr (Form != kDirectSteps && Form != kDirectTight) {
     // couplings of every node to the row below, as the chain reads them: zeros where they leave the row
     cplx<double>* scratch = x + a.max_nj;
     cplx<double>* lc = scratch + detail::kChainScratch;
@@ -118,16 +131,17 @@ __global__ void __launch_bounds__(NT) direct_solve_kernel(DirectArgs a) {
     if (tid == 0) lc[3 * nj] = czero<double>();
     __syncthreads();
     chain.solve(F, lc, t, x, scratch);
-  } else
-  // The two halves of the workgroup run the two sweeps of the twisted factorisation.  Up to 48 nodes wide the
-  // entries of two steps are loaded together, which hides part of their latency (16 subdomains of 35 nodes:
-  // 81 us one step at a time, 65 two, 66 three; 40 nodes: 86 two, 94 three); wider tiles stream
-  // their factors and are faster one step at a time (53 nodes, 256 subdomains: 179 us against 189 and 193).
-  if (nx <= 32) detail::twisted_solve_ring<8, 4, 8, NT / 2>(nx, ny, F, lower, t, x);
-  else if (nx <= 40) detail::twisted_solve_ring<4, 10, 2, NT / 2>(nx, ny, F, lower, t, x);
-  else if (nx <= 48) detail::twisted_solve_ring<4, 12, 2, NT / 2>(nx, ny, F, lower, t, x);
-  else if (nx <= 64) detail::twisted_solve_ring<4, 16, 1, NT / 2>(nx, ny, F, lower, t, x);
-  else detail::twisted_solve_plain<NT / 2>(nx, ny, F, lower, t, x);
+  } else {
+    // the two halves of the workgroup run the two sweeps of the twisted factorisation
+    constexpr bool kOwn = Form == kDirectSteps;
+    cplx<double>* own = x + a.max_nj;
+    if (nx <= 32) detail::twisted_solve_ring<8, 4, NT / 2, kOwn>(nx, ny, F, lower, t, x, own);
+    else if (nx <= 40) detail::twisted_solve_ring<4, 10, NT / 2, kOwn>(nx, ny, F, lower, t, x, own);
+    else if (nx <= 48) detail::twisted_solve_ring<4, 12, NT / 2, kOwn>(nx, ny, F, lower, t, x, own);
+    else if (nx <= 56) detail::twisted_solve_ring<4, 14, NT / 2, kOwn>(nx, ny, F, lower, t, x, own);
+    else if (nx <= 64) detail::twisted_solve_ring<4, 16, NT / 2, kOwn>(nx, ny, F, lower, t, x, own);
+    else detail::twisted_solve_plain<NT / 2>(nx, ny, F, lower, t, x);
+  }
   for (int n = tid; n < nj; n += NT) {
     if (a.U) a.U[(long long)rhs * a.nfine + d.off + n] = x[n];
     if (zout) {
@@ -159,7 +173,9 @@ static DirectKernel direct_kernel(int max_nj, int max_nx) {
     case kDirectNarrow: return direct_solve_kernel<kInnerThreads, kDirectNarrow>;
     case kDirectChain: return direct_solve_kernel<kInnerThreads, kDirectChain>;
     case kDirectWide: return direct_solve_kernel<kInnerThreads, kDirectWide>;
-    default: return direct_solve_kernel<kInnerThreads, kDirectSteps>;
+    case kDirectTall: return direct_solve_kernel<kInnerThreads, kDirectTall>;
+    case kDirectSteps: return direct_solve_kernel<kInnerThreads, kDirectSteps>;
+    default: return direct_solve_kernel<kInnerThreads, kDirectTight>;
   }
 }
 
