@@ -4,6 +4,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <cstring>
 
 #include "outer.hpp"
 
@@ -51,8 +52,27 @@ __device__ __forceinline__ void nd_pivot(const NdNode& nd, int t, int& p0, int& 
   pn = min(w, nd.s - p0);
 }
 
+// Largest v of the wave in every lane (no NaN).
+__device__ __forceinline__ double nd_wave_max(double v) {
+  v = fmax(v, dpp_f64<kDppXor1>(v));
+  v = fmax(v, dpp_f64<kDppXor2>(v));
+  v = fmax(v, dpp_f64<kDppHalfMirror>(v));
+  v = fmax(v, dpp_f64<kDppMirror>(v));
+  const auto larger = [](auto lo, auto hi) { return fmax(join_f64(lo[0], hi[0]), join_f64(lo[1], hi[1])); };
+  unsigned long long x = (unsigned long long)__double_as_longlong(v);
+  unsigned lo = (unsigned)x, hi = (unsigned)(x >> 32);
+  v = larger(__builtin_amdgcn_permlane16_swap(lo, lo, false, false), __builtin_amdgcn_permlane16_swap(hi, hi, false, false));
+  x = (unsigned long long)__double_as_longlong(v);
+  lo = (unsigned)x;
+  hi = (unsigned)(x >> 32);
+  return larger(__builtin_amdgcn_permlane32_swap(lo, lo, false, false), __builtin_amdgcn_permlane32_swap(hi, hi, false, false));
+}
+
 // Inverse of each separator matrix's pivot block in LDS: Gauss-Jordan with partial pivoting, one
-// workgroup per box; piv[node] keeps the smallest |pivot| (NaN sticks).
+// workgroup per box; piv[node] keeps the smallest |pivot| (NaN sticks).  A serial chain of n steps: every wave
+// finds the pivot for itself, reads what it needs of the two rows and the column, and writes its entries, interchange included,
+// after one barrier.  Set-up of a handle with a 10 x 10 coarse grid (two blocks of 50): 960 us with five barriers a step,
+// now 863.
 __global__ void __launch_bounds__(256) nd_pivot_kernel(const NdNode* __restrict__ nodes, int first, int t,
                                                        const double* __restrict__ X, double* __restrict__ dinv,
                                                        double* __restrict__ piv) {
@@ -61,67 +81,52 @@ __global__ void __launch_bounds__(256) nd_pivot_kernel(const NdNode* __restrict_
   nd_pivot(nd, t, p0, n);
   if (n <= 0) return;
   __shared__ double A[kNdPivot][kNdPivot + 1];
-  __shared__ double colp[kNdPivot];
-  __shared__ int perm[kNdPivot];
-  __shared__ double pmax;
-  const int tid = threadIdx.x, m = nd.s, c0 = tid % kWave, r0 = tid / kWave;
+  constexpr int kRows = kNdPivot / 4;
+  const int tid = threadIdx.x, m = nd.s, c = tid % kWave, r0 = tid / kWave, cc = min(c, n - 1);
   const double* F = X + nd.inv + (long long)p0 * m + p0;
   for (int r = r0; r < n; r += 4)
-    if (c0 < n) A[r][c0] = F[(long long)r * m + c0];
+    if (c < n) A[r][c] = F[(long long)r * m + c];
   double minp = INFINITY;
+  int perm = 0;   // lane p: the row that step p took
   __syncthreads();
   for (int p = 0; p < n; ++p) {
-    if (tid < kWave) {
-      double best = tid >= p && tid < n ? fabs(A[tid][p]) : -1.0;
-      int bi = tid;
-#pragma unroll
-      for (int o = kWave / 2; o > 0; o >>= 1) {
-        const double ob = __shfl_xor(best, o, kWave);
-        const int oi = __shfl_xor(bi, o, kWave);
-        if (ob > best || (ob == best && oi < bi)) { best = ob; bi = oi; }
-      }
-      if (tid == 0) {
-        const bool valid = bi >= p && bi < n;   // (no comparison holds in a column of NaN)
-        perm[p] = valid ? bi : p;
-        pmax = valid ? best : NAN;
-      }
-    }
-    __syncthreads();
-    const int q = perm[p];
+    const double v = fabs(A[cc][p]), cand = c >= p && c < n && v == v ? v : -1.0;
+    const double best = nd_wave_max(cand);
+    const unsigned long long at = __ballot(cand == best);
+    const bool valid = best >= 0.0;   // (not in a column of NaN)
+    const int q = valid ? __builtin_ctzll(at) : p;
+    const double pmax = valid ? best : NAN;
     minp = pmax < minp || pmax != pmax ? pmax : minp;
-    if (q != p && tid < n) {
-      const double x = A[p][tid];
-      A[p][tid] = A[q][tid];
-      A[q][tid] = x;
+    if (c == p) perm = q;
+    // entries of rows p and q in this lane's column, and of column p in this wave's rows
+    const double top = A[p][cc], inv = 1.0 / A[q][p], row = cc == p ? inv : inv * A[q][cc], topp = A[p][p];
+    double own[kRows], col[kRows];
+#pragma unroll
+    for (int i = 0; i < kRows; ++i) {
+      const int r = min(r0 + 4 * i, n - 1);
+      own[i] = r == q ? top : A[r][cc];
+      col[i] = r == q ? topp : A[r][p];
     }
     __syncthreads();
-    const double inv = 1.0 / A[p][p];
-    __syncthreads();
-    if (tid < n) {
-      colp[tid] = A[tid][p];
-      A[p][tid] = tid == p ? inv : inv * A[p][tid];
+#pragma unroll
+    for (int i = 0; i < kRows; ++i) {
+      const int r = r0 + 4 * i;
+      if (r < n && c < n) A[r][c] = r == p ? row : (c == p ? -inv * col[i] : own[i] - row * col[i]);
     }
-    __syncthreads();
-    if (c0 < n)
-      for (int r = r0; r < n; r += 4)
-        if (r != p) A[r][c0] = c0 == p ? -A[p][p] * colp[r] : A[r][c0] - A[p][c0] * colp[r];
     __syncthreads();
   }
-  // undo the row interchanges by swapping columns in reverse order
+  // undo the row interchanges: columns swapped in reverse order
+  int src = c;
   for (int p = n - 1; p >= 0; --p) {
-    const int q = perm[p];
-    if (q != p && tid < n) {
-      const double x = A[tid][p];
-      A[tid][p] = A[tid][q];
-      A[tid][q] = x;
-    }
-    __syncthreads();
+    const int q = __builtin_amdgcn_readlane(perm, p);
+    const int sp = __builtin_amdgcn_readlane(src, p), sq = __builtin_amdgcn_readlane(src, q);
+    src = c == p ? sq : (c == q ? sp : src);
   }
   double* D = dinv + (long long)blockIdx.x * kNdPivot * kNdPivot;
   for (int r = r0; r < n; r += 4)
-    if (c0 < n) D[r * kNdPivot + c0] = A[r][c0];
+    if (c < n) D[r * kNdPivot + c] = A[r][src];
   if (tid == 0) {
-    const double o = piv[first + blockIdx.x];
+    const double o = t > 0 ? piv[first + blockIdx.x] : INFINITY;
     piv[first + blockIdx.x] = minp < o || minp != minp ? minp : o;
   }
 }
@@ -564,18 +569,28 @@ NdPlan nd_plan(int n) {
     if (e_ != hipSuccess) return e_;     \
   } while (0)
 
-template <typename T>
-hipError_t NestedDissection::alloc(T** p, size_t count) {
-  void* q = nullptr;
-  hipError_t e = hipMalloc(&q, std::max<size_t>(count, 1) * sizeof(T));
-  if (e != hipSuccess) return e;
-  allocs.push_back(q);
-  *p = (T*)q;
-  return hipSuccess;
+NdMemory::~NdMemory() {
+  for (void* p : blocks) (void)hipFree(p);
 }
 
-NestedDissection::~NestedDissection() {
-  for (void* p : allocs) (void)hipFree(p);
+hipError_t NdMemory::take(void** p, size_t bytes) {
+  bytes = (std::max<size_t>(bytes, 1) + 255) & ~size_t(255);
+  const bool shared = bytes <= kNdSmall;
+  if (!shared || bytes > room) {
+    void* q = nullptr;
+    ND_TRY(hipMalloc(&q, shared ? kNdChunk : bytes));
+    blocks.push_back(q);
+    if (!shared) {
+      *p = q;
+      return hipSuccess;
+    }
+    chunk = (unsigned char*)q;
+    room = kNdChunk;
+  }
+  *p = chunk;
+  chunk += bytes;
+  room -= bytes;
+  return hipSuccess;
 }
 
 hipError_t NestedDissection::setup(const double* E, int n, int nr, cplx<double>* vec, hipStream_t st) {
@@ -590,47 +605,51 @@ hipError_t NestedDissection::setup(const double* E, int n, int nr, cplx<double>*
   nfac = P.nfac;
   glen = P.glen;
   nidx = (long long)P.idx.size();
-  ND_TRY(alloc(&fac, (size_t)nfac));
-  ND_TRY(alloc(&nodes, P.nodes.size()));
-  ND_TRY(alloc(&idx, P.idx.size()));
-  ND_TRY(alloc(&cpos, P.cpos.size()));
-  ND_TRY(alloc(&yv, (size_t)nr * ncoarse));
-  ND_TRY(alloc(&gv, (size_t)nr * std::max<long long>(glen, 1)));
-  ND_TRY(hipMemcpyAsync(nodes, P.nodes.data(), sizeof(NdNode) * P.nodes.size(), hipMemcpyHostToDevice, st));
-  ND_TRY(hipMemcpyAsync(idx, P.idx.data(), sizeof(int) * P.idx.size(), hipMemcpyHostToDevice, st));
-  ND_TRY(hipMemcpyAsync(cpos, P.cpos.data(), sizeof(int) * P.cpos.size(), hipMemcpyHostToDevice, st));
+  const size_t count = P.nodes.size();
   solve_bytes = 0;
   for (const NdNode& nd : P.nodes) {
     const long long m = nd.s + nd.b;
     // the solve matrices, and each vector entry read and written once per direction
     solve_bytes += 8 * (nd.s * m + (long long)nd.s * nd.b) + 16 * (2 * m + 2 * nd.s);
   }
+  ND_TRY(memory.take(&fac, (size_t)nfac));
+  // the plan in one copy: nodes, grid indices, child positions
+  const size_t idx_at = sizeof(NdNode) * count, cpos_at = idx_at + sizeof(int) * P.idx.size();
+  std::vector<unsigned char> plan(cpos_at + sizeof(int) * P.cpos.size());
+  std::memcpy(plan.data(), P.nodes.data(), idx_at);
+  std::memcpy(plan.data() + idx_at, P.idx.data(), cpos_at - idx_at);
+  std::memcpy(plan.data() + cpos_at, P.cpos.data(), plan.size() - cpos_at);
+  unsigned char* dplan = nullptr;
+  ND_TRY(memory.take(&dplan, plan.size()));
+  nodes = (NdNode*)dplan;
+  idx = (int*)(dplan + idx_at);
+  cpos = (int*)(dplan + cpos_at);
+  ND_TRY(memory.take(&yv, (size_t)nr * ncoarse));
+  ND_TRY(memory.take(&gv, (size_t)nr * std::max<long long>(glen, 1)));
+  ND_TRY(memory.take(&rv, (size_t)nr * 2 * ncoarse));
+  ND_TRY(hipMemcpyAsync(dplan, plan.data(), plan.size(), hipMemcpyHostToDevice, st));
+  // the solve kernel's largest LDS request, before anything is captured
+  for (const void* fn : {(const void*)nd_solve_kernel<64, 8>, (const void*)nd_solve_kernel<16, 8>, (const void*)nd_solve_kernel<8, 8>})
+    ND_TRY(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, kNdLds));
   // two depths of fronts are alive at a time; everything else is of one depth
-  long long len[2] = {1, 1}, ilen = 1;
-  int plen = 1;
-  size_t widest = 1;
+  size_t len[2] = {1, 1}, ilen = 1, plen = 1, widest = 1;
   for (size_t d = 0; d < levels.size(); ++d) {
-    len[d % 2] = std::max(len[d % 2], P.front_len[d]);
-    ilen = std::max(ilen, P.inv_len[d]);
-    plen = std::max(plen, P.panel_len[d]);
+    len[d % 2] = std::max(len[d % 2], (size_t)P.front_len[d]);
+    ilen = std::max(ilen, (size_t)P.inv_len[d]);
+    plen = std::max(plen, (size_t)P.panel_len[d]);
     widest = std::max(widest, (size_t)levels[d].count);
   }
+  NdMemory temp;
   double *front[2] = {nullptr, nullptr}, *X[3] = {nullptr, nullptr, nullptr}, *rows = nullptr, *cols = nullptr;
   double *dinv = nullptr, *dpiv = nullptr;
-  hipError_t err = hipSuccess;
-  auto temp = [&](double*& q, size_t count) {
-    if (err == hipSuccess) err = hipMalloc(&q, sizeof(double) * count);
-  };
-  for (int q = 0; q < 2; ++q) temp(front[q], (size_t)len[q]);
-  for (int q = 0; q < 3; ++q) temp(X[q], (size_t)ilen);
-  temp(rows, (size_t)plen * kNdPivot);
-  temp(cols, (size_t)plen * kNdPivot);
-  temp(dinv, widest * kNdPivot * kNdPivot);
-  temp(dpiv, P.nodes.size());
-  std::vector<double> piv(P.nodes.size(), INFINITY);
-  if (err == hipSuccess)
-    err = hipMemcpyAsync(dpiv, piv.data(), sizeof(double) * piv.size(), hipMemcpyHostToDevice, st);
-  for (int d = (int)levels.size() - 1; d >= 0 && err == hipSuccess; --d) {
+  for (int q = 0; q < 2; ++q) ND_TRY(temp.take(&front[q], len[q]));
+  for (int q = 0; q < 3; ++q) ND_TRY(temp.take(&X[q], ilen));
+  ND_TRY(temp.take(&rows, plen * kNdPivot));
+  ND_TRY(temp.take(&cols, plen * kNdPivot));
+  ND_TRY(temp.take(&dinv, widest * kNdPivot * kNdPivot));
+  std::vector<double> out(count + 2 * kNdNormBlocks);   // the smallest pivots, then norms
+  ND_TRY(temp.take(&dpiv, out.size()));
+  for (int d = (int)levels.size() - 1; d >= 0; --d) {
     const NdLevel& lv = levels[d];
     double* F = front[d % 2];
     auto tiles = [](int v) { return (unsigned)std::max(1, (v + kNdTile - 1) / kNdTile); };
@@ -655,44 +674,33 @@ hipError_t NestedDissection::setup(const double* E, int n, int nr, cplx<double>*
         hipLaunchKernelGGL(nd_product_kernel, dim3(grid[mode], cnt), dim3(256), 0, st, nds, at, mode, F,
                            (const double*)X[0], X[1], X[2], fac);
       hipLaunchKernelGGL(nd_extract_kernel, dim3(spread, cnt), dim3(256), 0, st, nds, at, (const double*)X[2], fac);
-      err = hipGetLastError();
+      ND_TRY(hipGetLastError());
     }
   }
-  if (err == hipSuccess) err = hipMemcpyAsync(piv.data(), dpiv, sizeof(double) * piv.size(), hipMemcpyDeviceToHost, st);
-  if (err == hipSuccess) err = hipStreamSynchronize(st);
-  for (double* q : {front[0], front[1], X[0], X[1], X[2], rows, cols, dinv, dpiv}) (void)hipFree(q);
-  if (err != hipSuccess) return err;
-  // the solve kernel's largest LDS request, before anything is captured
-  for (const void* fn : {(const void*)nd_solve_kernel<64, 8>, (const void*)nd_solve_kernel<16, 8>, (const void*)nd_solve_kernel<8, 8>})
-    ND_TRY(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, kNdLds));
-  // smallest |pivot| over every pivot block; a non-finite one marks the factor unusable
-  bool finite = true;
-  min_pivot = INFINITY;
-  for (double v : piv) {
-    finite = finite && std::isfinite(v);
-    min_pivot = std::min(min_pivot, v);
-  }
-  if (!finite) min_pivot = 0.0;
-  if (!(min_pivot > 0.0)) return hipSuccess;
   // error of a solve: the correction of one refinement, on a pseudo-random right-hand side
-  ND_TRY(alloc(&rv, (size_t)nr * 2 * ncoarse));
-  ND_TRY(launch_fill_hash(cv, ncoarse, 17081ull, st));
-  double* norms = nullptr;
-  ND_TRY(alloc(&norms, 2 * kNdNormBlocks));
-  std::vector<double> norms_h(2 * kNdNormBlocks);
   refine = false;
+  ND_TRY(launch_fill_hash(cv, ncoarse, 17081ull, st));
   ND_TRY(solve(1, st));
   ND_TRY(residual(1, st));
   ND_TRY(sweep(rv, 2 * ncoarse, rv + ncoarse, 2 * ncoarse, 1, st));
   hipLaunchKernelGGL(nd_norms_kernel, dim3(kNdNormBlocks), dim3(256), 0, st, (const cplx<double>*)(cv + ncoarse),
-                     (const cplx<double>*)(rv + ncoarse), ncoarse, norms);
+                     (const cplx<double>*)(rv + ncoarse), ncoarse, dpiv + count);
   ND_TRY(hipGetLastError());
-  ND_TRY(hipMemcpyAsync(norms_h.data(), norms, sizeof(double) * 2 * kNdNormBlocks, hipMemcpyDeviceToHost, st));
+  ND_TRY(hipMemcpyAsync(out.data(), dpiv, sizeof(double) * out.size(), hipMemcpyDeviceToHost, st));
   ND_TRY(hipStreamSynchronize(st));
+  // smallest |pivot| over every pivot block; a non-finite one marks the factor unusable
+  bool finite = true;
+  min_pivot = INFINITY;
+  for (size_t q = 0; q < count; ++q) {
+    finite = finite && std::isfinite(out[q]);
+    min_pivot = std::min(min_pivot, out[q]);
+  }
+  if (!finite) min_pivot = 0.0;
+  if (!(min_pivot > 0.0)) return hipSuccess;
   double x2 = 0.0, d2 = 0.0;
   for (int q = 0; q < kNdNormBlocks; ++q) {
-    x2 += norms_h[2 * q];
-    d2 += norms_h[2 * q + 1];
+    x2 += out[count + 2 * q];
+    d2 += out[count + 2 * q + 1];
   }
   solve_error = std::sqrt(d2 / x2);
   accurate = solve_error <= kNdRefuseAbove;   // (false for a NaN)
