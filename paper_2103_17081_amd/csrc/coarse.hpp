@@ -513,7 +513,10 @@ __device__ __forceinline__ void coarse_solve_paired(const SubDesc& d, const cplx
 
 // Form of the coarse solve, compiled into kernels of their own (a kernel's registers are those of
 // its largest form): the wave chain with 4 lanes per row (linear deflation, mx <= 16), with 2 lanes of
-// 13 columns (mx <= 26), or the step-by-step forms and the paired rows of Bezier deflation.
+// 13 columns (mx <= 26), or the step-by-step forms and the paired rows of Bezier deflation.  The chain of 13 columns
+// takes all 256 registers of a 512-thread kernel.  One tile past 53 nodes moves every subdomain of its
+// handle to the step-by-step form; an application of 16 complex64 solves then takes (us, twice the factor bytes and dependent
+// stored products -> two barriers -> this) 1097 -> 1029 -> 935 at 54 nodes, 1472 -> 1365 -> 1244 at 61, against 682 at 53.
 enum CoarseKind { kCoarseNarrow = 0, kCoarseChain = 1, kCoarseGeneral = 2 };
 constexpr int kNarrowMx = 16, kChainMx = 26;
 

@@ -11,8 +11,10 @@
 //   from the smallest boxes up:  y_S = b_S + sum of the children's g,  g_R = (children's g) - W y_S;
 //   from the largest box down:   x_S = Binv y_S - W^T x_R.
 // Every launch is a batch of independent dense products spread over the whole chip, and their
-// number is 2 log2(n / 10) + 1 for n x n unknowns.  A front of a box of width w holds 12 w^2
-// values in the two matrices kept, whatever its depth, so the factors grow as n^2 log n.
+// number is 2 log2(n / 10) + 1 for n x n unknowns (11 at n = 317).  The two matrices kept of a box of width w
+// that is cut inside the grid (s = 2 w, b = 4 w) hold s b + s (s + b) = 20 w^2 values, whatever its depth (12 w^2 for the
+// four below the whole grid, 4 w^2 for that), so the factors grow as n^2 log n; a smallest box holds about 166 w^2,
+// 103 of the 156 MB at n = 317.
 // (The block cyclic reduction over the grid's rows has n^3: at n = 317 it reads 0.90 GB per solve in
 // 21 launches.)
 // The set-up inverts F_SS by block Gauss-Jordan sweeps, batched over the boxes of a depth, with partial

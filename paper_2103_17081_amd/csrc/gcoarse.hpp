@@ -12,14 +12,17 @@
 //
 // E_0 is solved exactly in FP64 by one of two methods.  Coarse grids of at least
 // kNdIntervals intervals per wavelength take the nested dissection of dissection.hpp: fewer bytes,
-// launches and set-up operations (n = M-1 = 317: 338 -> 109 us per solve, 139 -> 41 ms for the set-up;
+// launches and set-up operations (n = M-1 = 317: 338 -> 109 us per solve, 139 -> 41 ms for the set-up of the k = 200 handle;
 // n = 636: 1814 -> 294 us, 1353 -> 33 ms), and a relative error of 3e-12 at most, unless the set-up finds
-// k^2 too near an eigenvalue of one of its boxes.  On coarser ones the
-// reduction's rounding error, which k^2 near an eigenvalue of one of its pivots raises, shows in the
-// result: over 500 grids of up to 400 intervals the two methods' corrections differ by more
-// than 1e-9 on 5 of 234 at 10 intervals per wavelength and on 23 of 266 at 5.  Results there are held
-// to what they were, so the reduction stays.  (At 10 the difference is the reduction's error: from residuals in
-// long double over 200 grids, 4e-5 at worst and above 1e-9 on 4, against 4.6e-12 for the dissection.)
+// k^2 too near an eigenvalue of one of its boxes.
+// The line at 8 is there for equal results, not for speed or accuracy.  Below it the two methods' corrections
+// differ by the reduction's rounding error, which k^2 near an eigenvalue of one of its pivots raises: by more than 1e-9
+// on 23 of 266 grids of up to 400 intervals at 5 per wavelength (5 of 234 at 10), and callers' results
+// there are kept as they were.  Measured on 72 grids of 12 to 220 intervals at 5 to 9 per wavelength, against
+// solutions refined in long double: relative error of the reduction 2e-15 to 1.1e-10, of the dissection 4e-16 to
+// 2.1e-12; us per solve 44 to 139 against 18 to 74, or 72 to 122 on the quarter of the grids whose solves the
+// dissection refines (there 0.8 to 1.2 times as fast as the reduction).  (At 10, from residuals in long double over 200 grids:
+// reduction 4e-5 at worst and above 1e-9 on 4, dissection 4.6e-12.)
 //
 // E_0 is block tridiagonal in the coarse rows (nb = M-1 blocks of n = M-1 unknowns).
 // In the block cyclic reduction, at every level the odd

@@ -360,7 +360,8 @@ hipError_t launch_conv(const ConvArgs& a, int batch, hipStream_t st) {
   const int mf = conv_mf(a.H, a.W, a.cinp, a.nb, batch);
   const dim3 grid((npix + 64 * mf - 1) / (64 * mf), batch);
   const size_t lds = conv_lds_bytes(a.H, a.W, a.cinp, mf);
-  // the largest layer taken: 160 KB of weight fragments and two-fragment band (128 channels into 64 are refused)
+  // Layers whose weight fragments and two-fragment band exceed 160 KB (128 channels into 64) are refused as they were
+  // when the weights lay in LDS beside the band; the kernel itself has room for them.
   const size_t weights = (size_t)a.ksteps * a.nb * kWave * sizeof(bf16x8);
   if (conv_lds_bytes(a.H, a.W, a.cinp, 2) + weights > 160 * 1024) return hipErrorInvalidValue;
   if (lds > 160 * 1024 || (1 << a.lc) != a.cinp || a.ksteps % kConvSteps || (a.mode == kUpCat && 2 * a.c1 != a.cinp))

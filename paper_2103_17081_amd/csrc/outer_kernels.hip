@@ -57,7 +57,6 @@ hipError_t launch_global_apply_masked(Consts cs, const cplx<double>* v, long lon
   return hipGetLastError();
 }
 
-// Advance the device-side outer step index (one thread).
 // w = f - w (restart residual), per right-hand side strides.
 __global__ void __launch_bounds__(256) residual_kernel(const cplx<double>* __restrict__ f, long long fstride,
                                                        cplx<double>* __restrict__ w, long long wstride,
