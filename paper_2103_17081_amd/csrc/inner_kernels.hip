@@ -63,24 +63,28 @@ struct Lds {
   double* cs;          // Givens cosines (maxit)
   double* scal;        // 8 scalars
   int* ctrl;           // 4 ints
-  cplx<double>* chain; // scratch of the coarse solve
+  cplx<double>* chain; // scratch of the coarse solve's narrow form
   int stride;          // maxit + 2
 };
 
-// Place of the coarse solve's scratch: tile A (rewritten by the prolongation), or where tile A is smaller, the
-// products cv (free until the operator is applied) if they are long enough, so that only short
-// bases of small tiles need extra room.
+// Place of the coarse solve's scratch: tile A (rewritten by the prolongation), made large enough.  Tiles that would
+// need more room for that (and the couplings' padding) than the coarse vectors save below take the products cv instead (free until the
+// operator is applied), if those are long enough.  Such tiles run the narrow form only: a block row of more
+// than 16 unknowns means at least 68 nodes and 17 coarse ones.
 constexpr size_t kChainBytes = detail::kChainScratch * sizeof(cplx<double>);
 
 template <typename T>
-__host__ __device__ bool scratch_in_cv(int max_nj, int maxit) {
-  return (size_t)max_nj * sizeof(cplx<T>) < kChainBytes && maxit + 2 >= detail::kChainScratch;
+__host__ __device__ bool scratch_in_cv(int max_nj, int max_nc, int maxit) {
+  const size_t tile = align16((size_t)max_nj * sizeof(cplx<T>));
+  return tile + 2 * (size_t)max_nc * sizeof(cplx<double>) < kChainBytes + 16 && maxit + 2 >= detail::kChainScratch;
 }
+static_assert(2 * (kNarrowMx + 1) * 2 * sizeof(cplx<float>) + 2 * (kNarrowMx + 1) * sizeof(cplx<double>) >= kChainBytes + 16,
+              "wider forms keep their scratch in tile A");
 
 template <typename T>
-__host__ __device__ size_t tile_a_bytes(int max_nj, int maxit) {
+__host__ __device__ size_t tile_a_bytes(int max_nj, int max_nc, int maxit) {
   const size_t tile = align16((size_t)max_nj * sizeof(cplx<T>));
-  return tile >= kChainBytes || scratch_in_cv<T>(max_nj, maxit) ? tile : kChainBytes;
+  return tile >= kChainBytes || scratch_in_cv<T>(max_nj, max_nc, maxit) ? tile : kChainBytes;
 }
 
 // The coarse vectors and the sums' wave partials share their place: the ones live within an
@@ -96,7 +100,7 @@ template <typename T>
 __host__ __device__ size_t lds_bytes(int max_nj, int max_nc, int maxit, int nt) {
   const size_t s = (size_t)maxit + 2;
   size_t b = 0;
-  b += tile_a_bytes<T>(max_nj, maxit) + align16((size_t)max_nj * sizeof(cplx<T>));
+  b += tile_a_bytes<T>(max_nj, max_nc, maxit) + align16((size_t)max_nj * sizeof(cplx<T>));
   b += align16(kClasses * kStencilPts * sizeof(cplx<T>));
   b += coarse_or_partials_bytes<T>(max_nc, maxit, nt);
   b += 2 * align16(s * sizeof(cplx<T>));
@@ -115,7 +119,7 @@ __device__ Lds<T> carve(unsigned char* base, int max_nj, int max_nc, int maxit) 
   L.stride = (int)s;
   size_t o = 0;
   auto take = [&](size_t bytes) { unsigned char* p = base + o; o += align16(bytes); return p; };
-  L.A = (cplx<T>*)take(tile_a_bytes<T>(max_nj, maxit));
+  L.A = (cplx<T>*)take(tile_a_bytes<T>(max_nj, max_nc, maxit));
   L.B = (cplx<T>*)take((size_t)max_nj * sizeof(cplx<T>));
   L.tab = (cplx<T>*)take(kClasses * kStencilPts * sizeof(cplx<T>));
   L.ct = (cplx<double>*)take(coarse_or_partials_bytes<T>(max_nc, maxit, NT));
@@ -132,7 +136,7 @@ __device__ Lds<T> carve(unsigned char* base, int max_nj, int max_nc, int maxit) 
   L.cs = (double*)take(s * sizeof(double));
   L.scal = (double*)take(8 * sizeof(double));
   L.ctrl = (int*)take(4 * sizeof(int));
-  L.chain = scratch_in_cv<T>(max_nj, maxit) ? L.cv : (cplx<double>*)L.A;
+  L.chain = scratch_in_cv<T>(max_nj, max_nc, maxit) ? L.cv : (cplx<double>*)L.A;
   return L;
 }
 
@@ -280,7 +284,8 @@ __device__ __forceinline__ void prolong_to(const SubDesc& d, const cplx<double>*
 template <typename T, int NT, int Kind>
 __device__ __forceinline__ void deflated_op(const SubDesc& d, const cplx<double>* fac, Lds<T>& L, bool apply,
                                             cplx<double>* keep) {
-  coarse_solve<NT, Kind>(d, fac, L.lc, L.ct, L.ca, L.chain, [&]() {
+  cplx<double>* scratch = Kind == kCoarseNarrow ? L.chain : reinterpret_cast<cplx<double>*>(L.A);
+  coarse_solve<NT, Kind>(d, fac, L.lc, L.ct, L.ca, scratch, [&]() {
     if (apply) {
       apply_B<T, false>(d, L.tab, L.A, L.B);
       lds_barrier();
